@@ -6,28 +6,33 @@
 //                                     negated for a row that holds a column twice (found
 //                                     with a column bitmap in LDS, or a hash table when
 //                                     n is large)
-//   pct_sap_iterate : k_sap_string    one wavefront per string, y in LDS (when n floats
+//                     k_sap_levels    which rows of a string can be projected side by side
+//   pct_sap_iterate : k_sap_levels    (only when the caller gives a row order)
+//                     k_sap_string    one workgroup per string, y in LDS (when n floats
 //                                     fit): y = x_k, then the relaxed projection of every
-//                                     row of the string in order; y_t to the workspace
-//                     k_sap_string_ws one workgroup of two wavefronts per string, y in the
-//                                     workspace: one wave loads the rows, the other
-//                                     projects them
+//                                     row of the string; y_t to the workspace
+//                     k_sap_string_ws one workgroup per string, y in the workspace: eight
+//                                     waves load the rows, eight project them
 //                     k_sap_average   x_{k+1}[j] = sum_t w_t y_t[j] in FP64, t in order
 //
-// A string is a chain of dependent row updates, so the parallelism is the number of
-// strings; one wavefront walks a row's entries 64 at a time.
+// A string is a chain of row updates, but rows that share no column commute.  A workgroup
+// takes the rows of its string in batches, one row per wave, and projects a batch level by
+// level (k_sap_levels): the same updates of every component of y in the same order, so the
+// result is the one of the rows taken one after another, bit for bit.  Measured per
+// iteration, 100 strings: 640,000 rows of the paper's 200 x 160 system 3.20 -> 0.67 ms
+// (one row at a time before), 368,640 curved rows on 400 x 400 5.85 -> 4.43 ms; with the
+// rows in a random order (nearly every pair shares a column) 2.95 -> 1.57 and 5.93 ->
+// 5.29 ms, since the loads and waits of the other rows leave the chain.
 //
-// LDS iterate: the rows' metadata is loaded 64 rows at a time (one row per lane) and the
-// first 384 entries of the next four rows are always in flight, so the wave waits on the
-// latency of HBM only once per several rows.  With one wave on its SIMD, every issued
-// instruction costs the wave its full issue slot, so a row is projected with only as many
+// LDS iterate: the metadata of 64 batches lies in the lanes of each wave, and the first 384
+// entries of its next two rows are always in flight.  A row is projected with only as many
 // chunks of 64 entries as it spans (a uniform branch on its length picks the body).
 //
 // Workspace iterate: each row update ends with a wait for its writes to y, and the
 // vector-memory counter retires in issue order, so that wait would also drain any row
-// loads in flight.  The loads therefore go to a second wavefront, which keeps two rows
-// in flight and stages each row (768 entries, values as binary32) in one of two LDS
-// slots; the two waves meet at a workgroup barrier once per row.  A row whose columns
+// loads in flight.  The loads therefore go to other wavefronts, which keep two rows each
+// in flight and stage each row (768 entries, values as binary32) in one of two LDS
+// slots; the waves meet at a workgroup barrier once per level.  A row whose columns
 // are distinct (the prepare pass marks the others) is written back with plain stores,
 // which stay in the XCD's L2 for the next row's gathers; global atomic adds would not.
 // The staged entries' gathers and stores go through a buffer resource over y: an entry
@@ -47,14 +52,18 @@ namespace {
 constexpr int SAP_WAVES_PREP = 4;   // waves per block of k_sap_prepare
 constexpr int SAP_HASH_BITS = 11;   // per-wave column table of k_sap_prepare: 2048 slots
 constexpr int SAP_HASH = 1 << SAP_HASH_BITS;
-// Ring of rows in flight: D rows ahead, the first PF chunks of 64 entries of each.  The
-// LDS iterate takes short rows from a long ring; the workspace iterate (large grids, long
-// curved rows) takes longer rows from a shorter ring.
-template <bool LDS> struct Ring { static constexpr int D = 4, PF = 6; };
+// Ring of rows in flight per wave: D rows ahead, the first PF chunks of 64 entries of each.
+// The LDS iterate takes short rows, the workspace iterate (large grids, long curved rows)
+// longer ones.
+template <bool LDS> struct Ring { static constexpr int D = 2, PF = 6; };
 template <> struct Ring<false> { static constexpr int D = 2, PF = 12; };
 
+// Rows of a string projected side by side (see k_sap_levels), one per wave: y in LDS, and
+// y in the workspace (there each row has a loading and a projecting wave).
+constexpr int SAP_W_LDS = 16, SAP_W_WS = 8;
+
 struct SapLayout {
-    size_t coef_off, w_off, y_off, total;
+    size_t coef_off, lev_off, w_off, y_off, total;
 };
 
 inline size_t a256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -62,7 +71,8 @@ inline size_t a256(size_t v) { return (v + 255) & ~size_t(255); }
 SapLayout sap_layout(int64_t m, int32_t n, int32_t M) {
     SapLayout L;
     L.coef_off = 256;   // [0, 256): status word (same header as the simulator workspace)
-    L.w_off = a256(L.coef_off + (size_t)m * sizeof(float));
+    L.lev_off = L.coef_off + (size_t)m * sizeof(float);   // one byte per position (k_sap_levels)
+    L.w_off = a256(L.lev_off + (size_t)m);
     L.y_off = a256(L.w_off + (size_t)M * sizeof(double));
     L.total = L.y_off + (size_t)M * (size_t)n * sizeof(float);
     return L;
@@ -77,6 +87,7 @@ struct SapArgs {
     const float *b;
     const int64_t *order;
     float *coef;
+    uint8_t *lev;   // per position: its level in its batch | (levels of the batch - 1) << 4
     int32_t *status;
 };
 
@@ -266,6 +277,92 @@ __device__ __forceinline__ RowMeta fetch_meta(const SapArgs &a, int64_t s, int64
     return r;
 }
 
+// Batches of a string's rows that can be projected side by side.  A string's positions go
+// in batches of W consecutive ones; two rows of a batch that share no column commute, bit
+// for bit (neither reads or writes a component of y that the other writes).  A row's level
+// is one more than the highest level among the batch's earlier rows that share a column
+// with it (0 without one), so that projecting the rows level by level gives every
+// component of y the same updates in the same order as row after row.  Consecutive rows of
+// a beam lie at random offsets of one or two angles: a batch of 16 rows of the paper's
+// 200 x 160 system has 1.7 levels on average, a batch of 8 curved rows on 400 x 400 1.4.
+//
+// One block of W waves per batch, each wave a row.  In LDS a mask of W bits per column
+// (of `span` columns at a time): every row sets its bit at its columns, then reads back
+// the bits of the others there, then clears them.
+template <int W>
+__global__ __launch_bounds__(64 * W) void k_sap_levels(SapArgs a, uint32_t span) {
+    static_assert(W == 8 || W == 16, "masks of 8 or 16 bits");
+    constexpr uint32_t PER = 32 / W, SH = W == 8 ? 2 : 1, MASK = (1u << W) - 1u;
+    constexpr int U = 8;   // chunks of 64 entries of the row kept in registers
+    extern __shared__ uint32_t tabs[];
+    __shared__ uint32_t conf[W];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t words = (span + PER - 1) / PER, n = (uint32_t)a.n;
+    for (uint32_t j = threadIdx.x; j < words; j += 64 * W) tabs[j] = 0u;
+    const int64_t longest = (a.m + a.M - 1) / a.M, per = (longest + W - 1) / W;
+    for (int64_t q = blockIdx.x; q < per * a.M; q += gridDim.x) {
+        const int64_t t = q / per, s0 = t * a.m / a.M, s1 = (t + 1) * a.m / a.M;
+        const int64_t p0 = s0 + (q - t * per) * W;
+        if (p0 >= s1) continue;   // the same for the whole block
+        const RowMeta r = fetch_meta(a, p0 + wave, s1);
+        int32_t c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t e = r.beg + u * 64 + lane;
+            c[u] = e < r.end ? a.cols[e] : -1;
+        }
+        const int64_t rest = r.beg + U * 64 + lane;
+        uint32_t met = 0u;
+        for (uint32_t lo = 0; lo < n; lo += span) {
+            const uint32_t len = n - lo < span ? n - lo : span;
+            __syncthreads();   // the table is clear
+            auto mark = [&](int32_t col) {
+                const uint32_t k = (uint32_t)col - lo;
+                if (k < len) atomicOr(&tabs[k >> SH], 1u << ((k & (PER - 1)) * W + wave));
+            };
+            auto read = [&](int32_t col) {
+                const uint32_t k = (uint32_t)col - lo;
+                if (k < len) met |= tabs[k >> SH] >> ((k & (PER - 1)) * W);
+            };
+            auto clear = [&](int32_t col) {
+                const uint32_t k = (uint32_t)col - lo;
+                if (k < len) tabs[k >> SH] = 0u;
+            };
+#pragma unroll
+            for (int u = 0; u < U; ++u) mark(c[u]);
+            for (int64_t e = rest; e < r.end; e += 64) mark(a.cols[e]);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u) read(c[u]);
+            for (int64_t e = rest; e < r.end; e += 64) read(a.cols[e]);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u) clear(c[u]);
+            for (int64_t e = rest; e < r.end; e += 64) clear(a.cols[e]);
+        }
+        for (int off = 32; off > 0; off >>= 1) met |= __shfl_xor(met, off, 64);
+        if (lane == 0) conf[wave] = met & MASK;
+        __syncthreads();
+        if (wave == 0) {
+            const uint32_t mine = lane < W ? conf[lane] : 0u;
+            int lv = 0;
+#pragma unroll
+            for (int v = 0; v < W; ++v) {   // lane v's level is final here
+                const int l = __builtin_amdgcn_readlane(lv, v) + 1;
+                if (lane > v && ((mine >> v) & 1u) && l > lv) lv = l;
+            }
+            int top = 0;
+#pragma unroll
+            for (int v = 0; v < W; ++v) {
+                const int l = __builtin_amdgcn_readlane(lv, v);
+                top = l > top ? l : top;
+            }
+            if (lane < W && p0 + lane < s1) a.lev[p0 + lane] = (uint8_t)(lv | (top << 4));
+        }
+        __syncthreads();   // conf is read before the next batch writes it
+    }
+}
+
 // The workspace copy of y, which only the string's own workgroup reads and writes
 // (workgroup scope).
 __device__ __forceinline__ float ws_load(float *y, int32_t c) {
@@ -318,13 +415,18 @@ __device__ __forceinline__ void project_chunks(const SapArgs &a, float *y, const
                                                int lane) {
     const uint32_t n = (uint32_t)a.n;
     bool ok[NC];
+    uint32_t at[NC];
+    // an entry past the row or with a bad column takes its lane's spare slot past y, which
+    // holds 0 (no branch)
 #pragma unroll
-    for (int k = 0; k < NC; ++k) ok[k] = (uint32_t)(k * 64 + lane) < len && (uint32_t)cc[k] < n;
-    // all gathers in flight before the first use; an entry past the row or with a bad
-    // column reads y[0] and counts 0
+    for (int k = 0; k < NC; ++k) {
+        ok[k] = (uint32_t)(k * 64 + lane) < len && (uint32_t)cc[k] < n;
+        at[k] = ok[k] ? (uint32_t)cc[k] : n + (uint32_t)lane;
+    }
+    // all gathers in flight before the first use
     float yv[NC];
 #pragma unroll
-    for (int k = 0; k < NC; ++k) yv[k] = y[ok[k] ? cc[k] : 0];
+    for (int k = 0; k < NC; ++k) yv[k] = y[at[k]];
     double acc = 0.0;
 #pragma unroll
     for (int k = 0; k < NC; ++k) acc = fma((double)(ok[k] ? widen(cv[k]) : 0.0f), (double)yv[k], acc);
@@ -339,14 +441,23 @@ __device__ __forceinline__ void project_chunks(const SapArgs &a, float *y, const
     }
     const double dot = wave_sum(acc);
     const float alpha = (float)(((double)r.b - dot) * (double)fabsf(r.coef));
-    // no branch: an entry that is not the row's adds 0 to its lane's spare slot past y
+    // distinct columns: y_c + alpha v stored, the arithmetic of the LDS atomic add, which
+    // takes several times as long per lane (16 rows of the paper's system side by side:
+    // 2.16 ms per iteration with atomic adds, 0.66 ms with stores)
+    if (r.coef > 0.0f) {
 #pragma unroll
-    for (int k = 0; k < NC; ++k)
-        atomicAdd(y + (ok[k] ? (uint32_t)cc[k] : n + (uint32_t)lane), ok[k] ? alpha * widen(cv[k]) : 0.0f);
+        for (int k = 0; k < NC; ++k) y[at[k]] = ok[k] ? yv[k] + alpha * widen(cv[k]) : 0.0f;
+    } else {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) atomicAdd(y + at[k], ok[k] ? alpha * widen(cv[k]) : 0.0f);
+    }
     if (tail) {
         for (int64_t e = r.beg + PF * 64 + lane; e < r.end; e += 64) {
             const int32_t c = a.cols[e];
-            if ((uint32_t)c < n) atomicAdd(y + c, alpha * val_at<VT>(a.vals, e));
+            if ((uint32_t)c >= n) continue;
+            const float av = alpha * val_at<VT>(a.vals, e);
+            if (r.coef > 0.0f) y[c] += av;
+            else atomicAdd(y + c, av);
         }
     }
 }
@@ -369,15 +480,21 @@ __device__ __forceinline__ void project_row(const SapArgs &a, float *y, const Ro
     }
 }
 
-// Metadata of 64 consecutive string positions, one per lane.
+// Metadata of 64 positions of a string, one per lane, STEP positions apart, and the levels
+// of their batches (`mine`: the position's own level, `top`: the highest of its batch).
 struct LaneMeta {
     int64_t beg, end;
     float b, coef;
+    int mine, top;
 };
 
-__device__ __forceinline__ LaneMeta lane_meta(const SapArgs &a, int64_t base, int64_t s1, int lane) {
-    const RowMeta r = fetch_meta(a, base + lane, s1);
-    return LaneMeta{r.beg, r.end, r.b, r.coef};
+// Positions p0 + lane * STEP + w; the batch of lane l starts at p0 + l * STEP.
+template <int STEP>
+__device__ __forceinline__ LaneMeta lane_meta(const SapArgs &a, int64_t p0, int w, int64_t s1, int lane) {
+    const int64_t first = p0 + (int64_t)lane * STEP, p = first + w;
+    const RowMeta r = fetch_meta(a, p, s1);
+    const int mine = p < s1 ? a.lev[p] & 15 : 0, top = first < s1 ? a.lev[first] >> 4 : 0;
+    return LaneMeta{r.beg, r.end, r.b, r.coef, mine, top};
 }
 
 // Position `idx` (uniform, < 64) of the lane-held metadata, as scalars.
@@ -393,55 +510,65 @@ __device__ __forceinline__ RowMeta meta_at(const LaneMeta &m, int idx) {
     return r;
 }
 
+// Barrier between the waves of a string: their LDS accesses before it happen before those
+// after it (lgkmcnt(0), s_barrier); global loads stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 template <typename VT>
-__global__ __launch_bounds__(64) void k_sap_string(SapArgs a, const float *x, float *Y) {
+__global__ __launch_bounds__(64 * SAP_W_LDS) void k_sap_string(SapArgs a, const float *x, float *Y) {
     extern __shared__ float ys[];
-    constexpr int D = Ring<true>::D, PF = Ring<true>::PF;
-    const int lane = threadIdx.x;
+    constexpr int D = Ring<true>::D, PF = Ring<true>::PF, W = SAP_W_LDS;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t = blockIdx.x;
     const int n = a.n;
     float *yg = Y + (size_t)t * (size_t)n;
     float *y = ys;
-    for (int j = lane; j < n; j += 64) y[j] = x[j];
+    for (int j = threadIdx.x; j < n; j += blockDim.x) y[j] = x[j];
+    if (wave == 0) y[n + lane] = 0.0f;   // the spare slots
     __syncthreads();
-    if (a.nnz == 0) {   // every row empty: nothing to load (and no entry to clamp to)
-        for (int j = lane; j < n; j += 64) yg[j] = ys[j];
-        return;
-    }
-
-    // The string's positions go in batches of 64 whose metadata the lanes hold (this
-    // batch in A, the next one in B).  Slot j of the ring holds the first PF chunks of
-    // the row at position j (mod D); a slot is refilled with the row D positions on as
-    // soon as its row is projected, so the loads of D rows are always in flight.
-    const int64_t s0 = (int64_t)t * a.m / a.M, s1 = (int64_t)(t + 1) * a.m / a.M;
-    LaneMeta A = lane_meta(a, s0, s1, lane), B = lane_meta(a, s0 + 64, s1, lane);
-    int32_t cq[D][PF];
-    typename RawOf<VT>::T vq[D][PF];
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        fetch_chunks<VT, PF>(a, meta_at(A, j), lane, cq[j], vq[j]);
-        __builtin_amdgcn_sched_barrier(0);   // slots filled in order
-    }
-    static_assert(64 % D == 0, "whole ring turns per batch");
-    for (int64_t sb = s0; sb < s1; sb += 64) {
-        // the position D on is in this batch, except in the batch's last ring turn
-        for (int j0 = 0; j0 < 64 - D; j0 += D) {
-#pragma unroll
-            for (int j = 0; j < D; ++j) {
-                project_row<VT, PF>(a, y, meta_at(A, j0 + j), cq[j], vq[j], lane);
-                fetch_chunks<VT, PF>(a, meta_at(A, j0 + j + D), lane, cq[j], vq[j]);
-            }
-        }
+    if (a.nnz > 0) {   // (else every row is empty: nothing to load, and no entry to clamp to)
+        // Batch k of the string is positions s0 + k W + wave, one per wave; the metadata of
+        // 64 batches lies in the lanes (this group in A, the next one in B).  Slot j of the
+        // ring holds the first PF chunks of the wave's row of batch j (mod D), refilled as
+        // soon as the batch is projected.
+        const int64_t s0 = (int64_t)t * a.m / a.M, s1 = (int64_t)(t + 1) * a.m / a.M;
+        const int64_t nb = (s1 - s0 + W - 1) / W;
+        LaneMeta A = lane_meta<W>(a, s0, wave, s1, lane), B = lane_meta<W>(a, s0 + 64 * W, wave, s1, lane);
+        int32_t cq[D][PF];
+        typename RawOf<VT>::T vq[D][PF];
 #pragma unroll
         for (int j = 0; j < D; ++j) {
-            project_row<VT, PF>(a, y, meta_at(A, 64 - D + j), cq[j], vq[j], lane);
-            fetch_chunks<VT, PF>(a, meta_at(B, j), lane, cq[j], vq[j]);
+            fetch_chunks<VT, PF>(a, meta_at(A, j), lane, cq[j], vq[j]);
+            __builtin_amdgcn_sched_barrier(0);   // slots filled in order
         }
-        A = B;
-        B = lane_meta(a, sb + 128, s1, lane);
+        static_assert(64 % D == 0, "whole ring turns per group");
+        for (int64_t k0 = 0; k0 < nb; k0 += 64) {
+            // whole ring turns: the batches past the string have no row and one level
+            const int kn = nb - k0 < 64 ? (int)(nb - k0) : 64;
+            for (int j0 = 0; j0 < kn; j0 += D) {
+#pragma unroll
+                for (int j = 0; j < D; ++j) {
+                    const RowMeta r = meta_at(A, j0 + j);
+                    const int mine = __builtin_amdgcn_readlane(A.mine, j0 + j);
+                    const int top = __builtin_amdgcn_readlane(A.top, j0 + j);
+                    for (int l = 0; l <= top; ++l) {   // the same count in every wave
+                        if (l == mine) project_row<VT, PF>(a, y, r, cq[j], vq[j], lane);
+                        lds_barrier();
+                    }
+                    const int nx = j0 + j + D;
+                    fetch_chunks<VT, PF>(a, nx < 64 ? meta_at(A, nx) : meta_at(B, nx - 64), lane, cq[j], vq[j]);
+                }
+            }
+            A = B;
+            B = lane_meta<W>(a, s0 + (k0 + 128) * W, wave, s1, lane);
+        }
     }
     __syncthreads();
-    for (int j = lane; j < n; j += 64) yg[j] = ys[j];
+    for (int j = threadIdx.x; j < n; j += blockDim.x) yg[j] = ys[j];
 }
 
 // Buffer access to a string's y (n binary32): an offset at or past 4 n bytes is outside
@@ -458,40 +585,85 @@ __device__ __forceinline__ void yb_store(__amdgpu_buffer_rsrc_t r, uint32_t off,
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, 1);
 }
 
-// Barrier between the two waves of k_sap_string_ws: their LDS accesses before it happen
-// before those after it (lgkmcnt(0), s_barrier); global loads stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+// One staged row projected onto y in the workspace (cf: its signed coefficient).  Its
+// updates are complete when it returns.
+template <typename VT>
+__device__ __forceinline__ void project_ws(const SapArgs &a, float *y, __amdgpu_buffer_rsrc_t yr, uint32_t nu,
+                                           const int32_t *sc, const float *sv, int64_t beg, int64_t end, float b,
+                                           float cf, int lane) {
+    constexpr int PF = Ring<false>::PF, SLOT = PF * 64;
+    if (cf == 0.0f) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");   // the other waves' updates before the barrier
+    const bool repeats = cf < 0.0f;   // some column twice: atomic adds
+    const float coef = fabsf(cf);
+    int32_t cc[PF];
+    float cv[PF], yv[PF];
+    bool ok[PF];
+#pragma unroll
+    for (int q = 0; q < PF; ++q) {
+        cc[q] = sc[q * 64 + lane];
+        cv[q] = sv[q * 64 + lane];
+        ok[q] = beg + q * 64 + lane < end && (uint32_t)cc[q] < nu;
+    }
+#pragma unroll
+    for (int q = 0; q < PF; ++q) yv[q] = yb_load(yr, ok[q] ? (uint32_t)cc[q] * 4u : Y_OUT);
+    double acc = 0.0;
+#pragma unroll
+    for (int q = 0; q < PF; ++q) acc = fma(ok[q] ? (double)cv[q] : 0.0, (double)yv[q], acc);
+    for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
+        const int32_t c = a.cols[e];
+        const bool okc = (uint32_t)c < nu;
+        const float yc = ws_load(y, okc ? c : 0);
+        acc = fma(okc ? (double)val_at<VT>(a.vals, e) : 0.0, (double)yc, acc);
+    }
+    const double dot = wave_sum(acc);
+    const float alpha = (float)(((double)b - dot) * (double)coef);
+    if (repeats) {
+#pragma unroll
+        for (int q = 0; q < PF; ++q)
+            if (ok[q]) ws_add(y, cc[q], alpha * cv[q]);
+        for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
+            const int32_t c = a.cols[e];
+            if ((uint32_t)c < nu) ws_add(y, c, alpha * val_at<VT>(a.vals, e));
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < PF; ++q) yb_store(yr, ok[q] ? (uint32_t)cc[q] * 4u : Y_OUT, yv[q] + alpha * cv[q]);
+        for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
+            const int32_t c = a.cols[e];
+            if ((uint32_t)c < nu) ws_put(y, c, ws_load(y, c) + alpha * val_at<VT>(a.vals, e));
+        }
+    }
+    ws_settle();
 }
 
 template <typename VT>
-__global__ __launch_bounds__(128) void k_sap_string_ws(SapArgs a, const float *x, float *Y) {
-    constexpr int D = Ring<false>::D, PF = Ring<false>::PF, SLOT = PF * 64;
-    __shared__ int32_t sc[2][SLOT];
-    __shared__ float sv[2][SLOT];
-    __shared__ int64_t sbeg[2], send[2];
-    __shared__ float sb[2], scoef[2];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+__global__ __launch_bounds__(128 * SAP_W_WS) void k_sap_string_ws(SapArgs a, const float *x, float *Y) {
+    constexpr int D = Ring<false>::D, PF = Ring<false>::PF, SLOT = PF * 64, W = SAP_W_WS;
+    __shared__ int32_t sc[2][W][SLOT];
+    __shared__ float sv[2][W][SLOT];
+    __shared__ int64_t sbeg[2][W], send[2][W];
+    __shared__ float sb[2][W], scoef[2][W];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int w = wave % W;   // the row of each batch that the wave loads or projects
     const int t = blockIdx.x;
     const int n = a.n;
     float *y = Y + (size_t)t * (size_t)n;
-    for (int j = threadIdx.x; j < n; j += 128) y[j] = x[j];
+    for (int j = threadIdx.x; j < n; j += 128 * W) y[j] = x[j];
     __syncthreads();   // (global and LDS) the copy is in L2 before the first gathers
-    if (a.nnz == 0) return;   // every row empty (both waves leave here)
+    if (a.nnz == 0) return;   // every row empty (all waves leave here)
 
     const int64_t s0 = (int64_t)t * a.m / a.M, s1 = (int64_t)(t + 1) * a.m / a.M;
-    const int64_t L = s1 - s0;
-    // Step k: the loader stages position k in slot k & 1 while the projector projects
-    // position k - 1 from slot (k - 1) & 1.  Both waves take the same number of steps
-    // (L + 1 rounded up to a multiple of D) and the barrier of each; positions past the
-    // string are empty rows (coefficient 0), so no step depends on a row's contents.
+    const int64_t nb = (s1 - s0 + W - 1) / W;
+    // Step k: the loaders stage batch k in slot k & 1 while the projectors project batch
+    // k - 1 from slot (k - 1) & 1, level by level.  All waves take the same number of steps
+    // (nb + 1 rounded up to a multiple of D) and the barriers of each (one per level of
+    // batch k - 1); rows past the string are empty (coefficient 0, level 0).
     static_assert(D % 2 == 0 && 64 % D == 0, "ring depth");
-    const int64_t steps = (L + D) / D * D;
-    if (wave == 1) {
+    const int64_t steps = (nb + D) / D * D;
+    LaneMeta A = lane_meta<W>(a, s0, w, s1, lane), B = lane_meta<W>(a, s0 + 64 * W, w, s1, lane);
+    if (wave >= W) {
         // loader: ring of D rows whose first SLOT entries are in flight
-        LaneMeta A = lane_meta(a, s0, s1, lane), B = lane_meta(a, s0 + 64, s1, lane);
         int32_t cq[D][PF];
         typename RawOf<VT>::T vq[D][PF];
         // the slots are filled in order (the scheduler may not interleave them), so a
@@ -501,89 +673,54 @@ __global__ __launch_bounds__(128) void k_sap_string_ws(SapArgs a, const float *x
             fetch_chunks<VT, PF>(a, meta_at(A, j), lane, cq[j], vq[j]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        for (int64_t sb0 = 0; sb0 < steps; sb0 += 64) {
-            const int jn = steps - sb0 < 64 ? (int)(steps - sb0) : 64;
+        int top = 0;   // of the batch being projected
+        for (int64_t k0 = 0; k0 < steps; k0 += 64) {
+            const int jn = steps - k0 < 64 ? (int)(steps - k0) : 64;
             for (int j0 = 0; j0 < jn; j0 += D) {
 #pragma unroll
                 for (int j = 0; j < D; ++j) {
-                    const int slot = j & 1;   // = k & 1, as sb0 and j0 are even
+                    const int slot = j & 1;   // = k & 1, as k0 and j0 are even
                     const RowMeta r = meta_at(A, j0 + j);
 #pragma unroll
                     for (int q = 0; q < PF; ++q) {
-                        sc[slot][q * 64 + lane] = cq[j][q];
-                        sv[slot][q * 64 + lane] = widen(vq[j][q]);
+                        sc[slot][w][q * 64 + lane] = cq[j][q];
+                        sv[slot][w][q * 64 + lane] = widen(vq[j][q]);
                     }
                     if (lane == 0) {
-                        sbeg[slot] = r.beg;
-                        send[slot] = r.end;
-                        sb[slot] = r.b;
-                        scoef[slot] = r.coef;
+                        sbeg[slot][w] = r.beg;
+                        send[slot][w] = r.end;
+                        sb[slot][w] = r.b;
+                        scoef[slot][w] = r.coef;
                     }
                     const int nx = j0 + j + D;
                     const RowMeta mn = nx < 64 ? meta_at(A, nx) : meta_at(B, nx - 64);
                     fetch_chunks<VT, PF>(a, mn, lane, cq[j], vq[j]);
-                    lds_barrier();
+                    for (int l = 0; l <= top; ++l) lds_barrier();
+                    top = __builtin_amdgcn_readlane(A.top, j0 + j);
                 }
             }
             A = B;
-            B = lane_meta(a, s0 + sb0 + 128, s1, lane);
+            B = lane_meta<W>(a, s0 + (k0 + 128) * W, w, s1, lane);
         }
     } else {
         // projector
         const uint32_t nu = (uint32_t)n;
         const __amdgpu_buffer_rsrc_t yr = y_rsrc(y, n);
-        for (int64_t k = 0; k < steps; ++k) {
-            if (k > 0) {
-                const int slot = (int)((k - 1) & 1);
-                const float cf = scoef[slot];
-                if (cf != 0.0f) {
-                    const bool repeats = cf < 0.0f;   // some column twice: atomic adds
-                    const float coef = fabsf(cf);
-                    const int64_t beg = sbeg[slot], end = send[slot];
-                    int32_t cc[PF];
-                    float cv[PF], yv[PF];
-                    bool ok[PF];
-#pragma unroll
-                    for (int q = 0; q < PF; ++q) {
-                        cc[q] = sc[slot][q * 64 + lane];
-                        cv[q] = sv[slot][q * 64 + lane];
-                        ok[q] = beg + q * 64 + lane < end && (uint32_t)cc[q] < nu;
-                    }
-#pragma unroll
-                    for (int q = 0; q < PF; ++q) yv[q] = yb_load(yr, ok[q] ? (uint32_t)cc[q] * 4u : Y_OUT);
-                    double acc = 0.0;
-#pragma unroll
-                    for (int q = 0; q < PF; ++q) acc = fma(ok[q] ? (double)cv[q] : 0.0, (double)yv[q], acc);
-                    for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
-                        const int32_t c = a.cols[e];
-                        const bool okc = (uint32_t)c < nu;
-                        const float yc = ws_load(y, okc ? c : 0);
-                        acc = fma(okc ? (double)val_at<VT>(a.vals, e) : 0.0, (double)yc, acc);
-                    }
-                    const double dot = wave_sum(acc);
-                    const float alpha = (float)(((double)sb[slot] - dot) * (double)coef);
-                    if (repeats) {
-#pragma unroll
-                        for (int q = 0; q < PF; ++q)
-                            if (ok[q]) ws_add(y, cc[q], alpha * cv[q]);
-                        for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
-                            const int32_t c = a.cols[e];
-                            if ((uint32_t)c < nu) ws_add(y, c, alpha * val_at<VT>(a.vals, e));
-                        }
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < PF; ++q)
-                            yb_store(yr, ok[q] ? (uint32_t)cc[q] * 4u : Y_OUT, yv[q] + alpha * cv[q]);
-                        for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
-                            const int32_t c = a.cols[e];
-                            if ((uint32_t)c < nu) ws_put(y, c, ws_load(y, c) + alpha * val_at<VT>(a.vals, e));
-                        }
-                    }
-                    // the next row's gathers must see these adds
-                    ws_settle();
+        lds_barrier();   // step 0: nothing is staged yet
+        for (int64_t k0 = 0; k0 < steps - 1; k0 += 64) {
+            const int jn = steps - 1 - k0 < 64 ? (int)(steps - 1 - k0) : 64;
+            for (int j = 0; j < jn; ++j) {
+                const int slot = j & 1;   // batch k0 + j, k0 even
+                const int mine = __builtin_amdgcn_readlane(A.mine, j), top = __builtin_amdgcn_readlane(A.top, j);
+                for (int l = 0; l <= top; ++l) {
+                    if (l == mine) project_ws<VT>(a, y, yr, nu, sc[slot][w], sv[slot][w], sbeg[slot][w], send[slot][w],
+                                                  sb[slot][w], scoef[slot][w], lane);
+                    // the next level's gathers, by any wave, see this level's updates
+                    lds_barrier();
                 }
             }
-            lds_barrier();
+            A = B;
+            B = lane_meta<W>(a, s0 + (k0 + 128) * W, w, s1, lane);
         }
     }
 }
@@ -599,6 +736,10 @@ __global__ void k_sap_average(const float *Y, const double *w, int32_t M, int32_
 __global__ void k_sap_uniform(double *w, int32_t M) {
     const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t < M) w[t] = 1.0 / (double)M;
+}
+
+__global__ void k_sap_no_levels(uint8_t *lev, int64_t m) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) lev[i] = 0;
 }
 
 __global__ void k_sap_clear_status(int32_t *status) {
@@ -641,6 +782,7 @@ SapArgs make_args(const pct_csr *A, const pct_sap *p, char *ws, const SapLayout 
     a.b = A->b_dev;
     a.order = p->order_dev;
     a.coef = (float *)(ws + L.coef_off);
+    a.lev = (uint8_t *)(ws + L.lev_off);
     a.status = (int32_t *)ws;
     return a;
 }
@@ -653,17 +795,52 @@ size_t lds_limit() {
     return v > 0 ? (size_t)v : 0;
 }
 
+// Whether a string's iterate (and one spare slot per lane, the target of the adds of
+// entries past a row) fits a workgroup's LDS.
+bool y_in_lds(int32_t n) { return ((size_t)n + 64) * sizeof(float) <= lds_limit(); }
+
+// Positions of the longest string.
+int64_t longest_string(const SapArgs &a) { return (a.m + a.M - 1) / a.M; }
+
+// The levels of every batch of the strings (k_sap_levels), for the iterate that n takes.
+template <int W>
+pct_status launch_levels_w(const SapArgs &a, hipStream_t s) {
+    const size_t room = lds_limit() > 1024 ? (lds_limit() - 1024) & ~size_t(15) : 0;
+    const size_t cols = room * 8 / W;   // W bits per column
+    const uint32_t span = (size_t)a.n < cols ? (uint32_t)a.n : (uint32_t)cols;
+    if (span == 0) return PCT_EHIP;
+    const size_t bytes = ((size_t)span * W / 8 + 3) / 4 * 4 + 4;
+    const int64_t per = (longest_string(a) + W - 1) / W, batches = per * a.M;
+    const unsigned blocks = (unsigned)(batches < 2048 ? batches : 2048);
+    if (hipFuncSetAttribute((const void *)k_sap_levels<W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) !=
+        hipSuccess)
+        return PCT_EHIP;
+    hipLaunchKernelGGL((k_sap_levels<W>), dim3(blocks), dim3(64 * W), bytes, s, a, span);
+    return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
+}
+pct_status launch_levels(const SapArgs &a, hipStream_t s) {
+    if (a.m == 0 || a.nnz == 0) return PCT_OK;   // no row to project
+    if (longest_string(a) == 1) {                // every batch is one row
+        const int64_t blocks = (a.m + 255) / 256;
+        hipLaunchKernelGGL(k_sap_no_levels, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, s, a.lev, a.m);
+        return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
+    }
+    return y_in_lds(a.n) ? launch_levels_w<SAP_W_LDS>(a, s) : launch_levels_w<SAP_W_WS>(a, s);
+}
+
 template <typename VT>
 pct_status launch_strings(const SapArgs &a, const float *x, float *Y, hipStream_t s) {
-    // y and one spare slot per lane (the target of the adds of entries past a row)
     const size_t bytes = ((size_t)a.n + 64) * sizeof(float);
-    if (bytes <= lds_limit()) {
+    if (y_in_lds(a.n)) {
         if (hipFuncSetAttribute((const void *)k_sap_string<VT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)bytes) != hipSuccess)
             return PCT_EHIP;
-        hipLaunchKernelGGL((k_sap_string<VT>), dim3((unsigned)a.M), dim3(64), bytes, s, a, x, Y);
+        // strings shorter than a batch: only the waves that have a row
+        const int64_t waves = longest_string(a) < SAP_W_LDS ? longest_string(a) : SAP_W_LDS;
+        hipLaunchKernelGGL((k_sap_string<VT>), dim3((unsigned)a.M), dim3(64 * (unsigned)(waves > 1 ? waves : 1)), bytes,
+                           s, a, x, Y);
     } else {
-        hipLaunchKernelGGL((k_sap_string_ws<VT>), dim3((unsigned)a.M), dim3(128), 0, s, a, x, Y);
+        hipLaunchKernelGGL((k_sap_string_ws<VT>), dim3((unsigned)a.M), dim3(128 * SAP_W_WS), 0, s, a, x, Y);
     }
     return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
 }
@@ -724,7 +901,8 @@ pct_status pct_sap_prepare(const pct_csr *A, const pct_sap *p, void *ws_dev, siz
                                p->relax);
         }
     }
-    return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
+    if (hipGetLastError() != hipSuccess) return PCT_EHIP;
+    return p->order_dev ? PCT_OK : launch_levels(a, s);
 }
 
 pct_status pct_sap_iterate(const pct_csr *A, const pct_sap *p, float *x_dev, int32_t n_iter, void *ws_dev,
@@ -741,6 +919,12 @@ pct_status pct_sap_iterate(const pct_csr *A, const pct_sap *p, float *x_dev, int
     float *Y = (float *)(ws + L.y_off);
     const double *w = (const double *)(ws + L.w_off);
     const unsigned avg_blocks = (unsigned)((A->n_cols + 255) / 256);
+    // the levels of the natural order are the prepare pass's; those of an order given by
+    // the caller are taken from what its buffer holds now
+    if (p->order_dev && n_iter > 0) {
+        const pct_status ls = launch_levels(a, s);
+        if (ls != PCT_OK) return ls;
+    }
     for (int32_t it = 0; it < n_iter; ++it) {
         const pct_status ls = A->val_dtype == PCT_F16 ? launch_strings<__half>(a, x_dev, Y, s)
                                                       : launch_strings<float>(a, x_dev, Y, s);
