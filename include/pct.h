@@ -229,7 +229,8 @@ pct_status pct_device_status(const void *ws_dev, void *stream);
                             /* time first), so that cheap tiles fill the tail           */
 
 typedef struct {
-    int32_t rows_per_wave;  /* 16, 32 or 64: consecutive rows walked by one wavefront    */
+    int32_t rows_per_wave;  /* 16, 32 or 64: consecutive rows walked by one wavefront;   */
+                            /* fewer where the batch has too few rows to fill the device */
     int32_t order;          /* PCT_ORDER_GIVEN | PCT_ORDER_LPT (within each grid          */
                             /* dimension: the emit takes the 2D jobs, then the 3D jobs)  */
     int32_t blocks_per_cu;  /* 0: one block of 4 wavefronts per emit tile, a grid over   */

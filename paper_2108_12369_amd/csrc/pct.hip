@@ -1058,6 +1058,21 @@ static void tune_store(uint64_t key, const pct_launch_config &cfg) {
     fclose(f);
 }
 
+// Rows per wavefront of the emit: the configured number, or, for a batch too small to give
+// every wave slot of the device EMIT_ROUNDS waves at that number, the largest power of two
+// that does (at least 1): rows of one wave follow one another, 2 us or so each, so with 64
+// of them 1,440 straight rows took 165 us on 23 waves.  Calls of 92,160 straight 2D, 100,003
+// curved 3D (WEPL only) and 300,001 straight 3D rows, us: 220, 440, 414 with 64 rows per
+// wave; with at least 1, 2, 4 or 8 waves per slot 140, 301, 414; 131, 277, 357; 127, 270,
+// 336; 131, 273, 332 (a wave's start costs about one row).
+constexpr int EMIT_ROUNDS = 4;
+static int rows_per_wave(int32_t configured, int64_t total_rows) {
+    const int64_t slots = (int64_t)cu_count() * 16;   // 4 SIMDs x 4 waves of the emit kernel
+    int r = configured;
+    while (r > 1 && total_rows < slots * EMIT_ROUNDS * r) r >>= 1;
+    return r;
+}
+
 // Relative cost of one row of a job: voxels a path crosses (about the sum of the grid
 // sizes) plus, for spline paths, the samples over an outer-boundary diameter.
 static double row_cost(const pct_job &jb) {
@@ -1191,11 +1206,12 @@ static pct_status prepare(int32_t n_jobs, const pct_job *jobs, void *ws, size_t 
     } else {
         std::stable_sort(order, order + n_jobs, before);
     }
-    const int64_t rows_per_etile = (int64_t)(TILE / WAVE) * cfg.rows_per_wave;
+    const int rpw = rows_per_wave(cfg.rows_per_wave, P.L.total_rows);
+    const int64_t rows_per_etile = (int64_t)(TILE / WAVE) * rpw;
     int64_t etile = 0;
     for (int k = 0; k < n_jobs; ++k) {
         JobDev &J = jd[order[k]];
-        J.rpw = cfg.rows_per_wave;
+        J.rpw = rpw;
         J.etile_base = etile;
         J.n_etiles = (J.row_count + rows_per_etile - 1) / rows_per_etile;
         const int di = J.dim == 3 ? 1 : 0;
