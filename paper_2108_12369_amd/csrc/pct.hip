@@ -338,22 +338,58 @@ __global__ void __launch_bounds__(TILE) k_row_ptr(const JobDev *__restrict__ job
     if (r < J.row_count) J.row_ptr[r] = base + sc[threadIdx.x] - c;
 }
 
-// Wave-cooperative emit: each wavefront of the block takes 64 rows of the tile.
-
-// One instance per grid dimension (the register needs differ), launched over that
-// dimension's emit tiles only: they are one range, [tile_base, tile_base + gridDim.x),
-// of the launch order.  A block is one emit tile: 4 waves of rpw rows.
+// Rows whose spline may leave the grid box, or with more entries than a wave stages: one
+// lane per row of a count tile.
 template <typename R, bool STORE, int DIM>
-__global__ void __launch_bounds__(TILE) k_emit_wave(const JobDev *__restrict__ jobs, const int32_t *__restrict__ eorder,
-                                                    int n_jobs, char *__restrict__ rowbuf,
-                                                    int32_t *__restrict__ status, int64_t tile_base) {
+__device__ __forceinline__ void emit_lane_tile(const JobDev *jobs, const int32_t *corder, int n_jobs, char *rowbuf,
+                                               int64_t tile, int32_t *status) {
+    const JobDev &J = jobs[job_of_tile(jobs, corder, n_jobs, tile)];
+    if (J.dim != DIM) return;
+    const int64_t r = (tile - J.tile_base) * TILE + threadIdx.x;
+    if (r >= J.row_count) return;
+    const RowRefD<R, DIM> w = row_ref<R, DIM>(rowbuf, J, r);
+    if (RV(w, kind) == 3) emit_row_lane<R, DIM, STORE>(J, w, r, status);
+}
+
+// The count tiles [base, base + tiles) of one grid dimension for the per-lane walk, `per`
+// (1 to 64) of them to each of the first `blocks` blocks of an emit launch (blocks 0: none).
+struct LaneTiles {
+    int64_t base, tiles;
+    int32_t per, blocks;
+};
+
+// Wave-cooperative emit.  One instance per grid dimension (the register needs differ),
+// launched over that dimension's emit tiles only: they are one range, from tile_base on, of
+// the launch order.  A block is one emit tile: 4 waves of rpw rows.
+// LANES: the launch's first blocks take the rows of the per-lane walk.  A handful of such
+// rows (curved 3D paths near a pole that touches the grid box) takes 0.25 ms, a lane walking
+// some 600 chords, which a launch of its own added to the call; here the other blocks run
+// beside it (1M curved 3D rows, 200 x 200 x 160: 2.47 -> 2.20 ms; a 5M-row chunk on 256 x
+// 256 x 160: 10.3 -> 9.85 ms).  4 waves per SIMD, as without it: the per-lane walk's spills
+// stay in its own blocks.  In 2D, where such rows are rarer, the scratch it needs cost
+// every wave more than the launch (curved rows 0.6% slower): k_emit_lane there.
+template <typename R, bool STORE, int DIM, bool LANES>
+__global__ void __launch_bounds__(TILE, LANES ? 4 : 1)
+k_emit_wave(const JobDev *__restrict__ jobs, const int32_t *__restrict__ eorder, int n_jobs, char *__restrict__ rowbuf,
+            const int32_t *__restrict__ tile_flags, int32_t *__restrict__ status, int64_t tile_base, LaneTiles lt) {
     __shared__ __attribute__((aligned(16))) uint2 stage[TILE / WAVE][STAGE_CAP + 1];   // 1024 slots per wave
-    const int64_t tile = tile_base + blockIdx.x;
+    const int lane = threadIdx.x % WAVE;
+    int64_t tile = tile_base + blockIdx.x;
+    if constexpr (LANES) {
+        if ((int32_t)blockIdx.x < lt.blocks) {
+            const int64_t t0 = (int64_t)blockIdx.x * lt.per, tl = t0 + lane;
+            const bool some = lane < lt.per && tl < lt.tiles && tile_flags[lt.base + tl] != 0;
+            for (uint64_t todo = __builtin_amdgcn_ballot_w64(some); todo != 0; todo &= todo - 1)
+                emit_lane_tile<R, STORE, DIM>(jobs, eorder + n_jobs, n_jobs, rowbuf,
+                                              lt.base + t0 + __builtin_ctzll(todo), status);
+            return;
+        }
+        tile -= lt.blocks;
+    }
     const int jid = job_of_etile(jobs, eorder, n_jobs, tile);
     const JobDev &J = jobs[jid];
     if (J.dim != DIM) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int lane = threadIdx.x % WAVE;
     const int64_t r0 = ((tile - J.etile_base) * (TILE / WAVE) + wave) * J.rpw;
     emit_rows_wave<R, DIM, STORE>(J, rowbuf, r0, J.rpw, lane, stage[wave], status);
 }
@@ -394,25 +430,15 @@ __global__ void __launch_bounds__(TILE) k_emit_queue(const JobDev *__restrict__ 
     }
 }
 
-// Rows whose spline may leave the grid box: one lane per row.
-template <typename R, bool STORE>
+// The per-lane walk in a launch of its own, over the count tiles of one grid dimension.
+template <typename R, bool STORE, int DIM>
 __global__ void __launch_bounds__(TILE) k_emit_lane(const JobDev *__restrict__ jobs, const int32_t *__restrict__ corder,
                                                     int n_jobs, char *__restrict__ rowbuf,
                                                     const int32_t *__restrict__ tile_flags,
-                                                    int32_t *__restrict__ status) {
-    const int64_t tile = blockIdx.x;
+                                                    int32_t *__restrict__ status, int64_t tile_base) {
+    const int64_t tile = tile_base + blockIdx.x;
     if (tile_flags[tile] == 0) return;   // no row of this tile needs the per-lane walk
-    const int jid = job_of_tile(jobs, corder, n_jobs, tile);
-    const JobDev &J = jobs[jid];
-    const int64_t r = (tile - J.tile_base) * TILE + threadIdx.x;
-    if (r >= J.row_count) return;
-    if (J.dim == 3) {
-        const RowRefD<R, 3> w = row_ref<R, 3>(rowbuf, J, r);
-        if (RV(w, kind) == 3) emit_row_lane<R, 3, STORE>(J, w, r, status);
-    } else {
-        const RowRefD<R, 2> w = row_ref<R, 2>(rowbuf, J, r);
-        if (RV(w, kind) == 3) emit_row_lane<R, 2, STORE>(J, w, r, status);
-    }
+    emit_lane_tile<R, STORE, DIM>(jobs, corder, n_jobs, rowbuf, tile, status);
 }
 
 // ---------------------------------------------------------------- phantom build
@@ -1131,6 +1157,7 @@ struct Prepared {
     int64_t total_etiles = 0;
     int64_t dim_base[2] = {0, 0}, dim_tiles[2] = {0, 0};   // emit tiles of the 2D jobs, then the 3D jobs
     int64_t cdim_base[2] = {0, 0}, cdim_tiles[2] = {0, 0}; // count tiles likewise
+    bool lane_rows[2] = {false, false};                      // 2D, 3D: rows of the per-lane walk are possible
     bool any_bricks = false;                                 // some job has a bricked copy of x to fill
     explicit Prepared(int32_t n) : H(n) {}
 };
@@ -1179,6 +1206,8 @@ static pct_status prepare(int32_t n_jobs, const pct_job *jobs, void *ws, size_t 
             const int di = J.dim == 3 ? 1 : 0;
             if (P.cdim_tiles[di] == 0) P.cdim_base[di] = tile;
             P.cdim_tiles[di] += J.n_tiles;
+            // a straight row crosses each face plane of the grid at most once
+            if (J.path != PCT_STRAIGHT || (int64_t)J.n[0] + J.n[1] + J.n[2] > STAGE_CAP) P.lane_rows[di] = true;
             tile += J.n_tiles;
         }
     }
@@ -1243,32 +1272,52 @@ static pct_status prepare(int32_t n_jobs, const pct_job *jobs, void *ws, size_t 
     return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
 }
 
-// The emit kernels of one call: per grid dimension either a grid over its tiles or a
-// persistent grid that takes them from a queue; then the per-lane kernel.
+// The count tiles of a grid dimension (0: 2D, 1: 3D) over the leading blocks of its emit
+// launch: one each, or, past the 1,024 blocks that fill the device, several (an empty block
+// costs about as much as reading one more flag).
+static LaneTiles lane_tiles(const Prepared &P, int d) {
+    const int64_t n = P.cdim_tiles[d], per = std::min<int64_t>((n + 1023) / 1024, WAVE);
+    return P.lane_rows[d] ? LaneTiles{P.cdim_base[d], n, (int32_t)per, (int32_t)((n + per - 1) / per)}
+                          : LaneTiles{0, 0, 1, 0};
+}
+
+template <typename R, bool STORE, int DIM>
+static void launch_lane(const Prepared &P, hipStream_t s, const JobDev *J, const int32_t *eorder, int n_jobs, char *rb,
+                        const int32_t *flags, int32_t *status) {
+    if (P.lane_rows[DIM - 2] && P.cdim_tiles[DIM - 2] > 0)
+        hipLaunchKernelGGL((k_emit_lane<R, STORE, DIM>), dim3((unsigned)P.cdim_tiles[DIM - 2]), dim3(TILE), 0, s, J,
+                           eorder + n_jobs, n_jobs, rb, flags, status, P.cdim_base[DIM - 2]);
+}
+
+// The emit kernels of one call: per grid dimension either a grid over its tiles (in 3D with
+// the per-lane walk in it) or a persistent grid that takes them from a queue; then the
+// per-lane kernels.
 template <typename R, bool STORE>
 static void launch_emit(const Prepared &P, bool has2, bool has3, hipStream_t s, const JobDev *J,
-                        const int32_t *eorder, int n_jobs, char *rb, int32_t *flags, int32_t *status, WsHeader *hdr,
-                        dim3 grid) {
+                        const int32_t *eorder, int n_jobs, char *rb, int32_t *flags, int32_t *status, WsHeader *hdr) {
     const dim3 block(TILE);
+    const int64_t n2 = has2 ? P.dim_tiles[0] : 0, n3 = has3 ? P.dim_tiles[1] : 0;
     if (P.cfg.blocks_per_cu > 0) {
         hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(64), 0, s, hdr);
         const int64_t cap = (int64_t)cu_count() * P.cfg.blocks_per_cu;
-        const int64_t n2 = has2 ? P.dim_tiles[0] : 0, n3 = has3 ? P.dim_tiles[1] : 0;
         if (n2 > 0)
             hipLaunchKernelGGL((k_emit_queue<R, STORE, 2>), dim3((unsigned)(n2 < cap ? n2 : cap)), block, 0, s, J,
                                eorder, n_jobs, rb, status, &hdr->qnext[0], P.dim_base[0], n2);
         if (n3 > 0)
             hipLaunchKernelGGL((k_emit_queue<R, STORE, 3>), dim3((unsigned)(n3 < cap ? n3 : cap)), block, 0, s, J,
                                eorder, n_jobs, rb, status, &hdr->qnext[1], P.dim_base[1], n3);
+        launch_lane<R, STORE, 3>(P, s, J, eorder, n_jobs, rb, flags, status);
     } else {
-        if (has2 && P.dim_tiles[0] > 0)
-            hipLaunchKernelGGL((k_emit_wave<R, STORE, 2>), dim3((unsigned)P.dim_tiles[0]), block, 0, s, J, eorder,
-                               n_jobs, rb, status, P.dim_base[0]);
-        if (has3 && P.dim_tiles[1] > 0)
-            hipLaunchKernelGGL((k_emit_wave<R, STORE, 3>), dim3((unsigned)P.dim_tiles[1]), block, 0, s, J, eorder,
-                               n_jobs, rb, status, P.dim_base[1]);
+        if (n2 > 0)
+            hipLaunchKernelGGL((k_emit_wave<R, STORE, 2, false>), dim3((unsigned)n2), block, 0, s, J, eorder, n_jobs,
+                               rb, flags, status, P.dim_base[0], LaneTiles{0, 0, 1, 0});
+        if (n3 > 0) {
+            const LaneTiles lt = lane_tiles(P, 1);
+            hipLaunchKernelGGL((k_emit_wave<R, STORE, 3, true>), dim3((unsigned)(lt.blocks + n3)), block, 0, s, J,
+                               eorder, n_jobs, rb, flags, status, P.dim_base[1], lt);
+        }
     }
-    hipLaunchKernelGGL((k_emit_lane<R, STORE>), grid, block, 0, s, J, eorder + n_jobs, n_jobs, rb, flags, status);
+    launch_lane<R, STORE, 2>(P, s, J, eorder, n_jobs, rb, flags, status);
 }
 
 }  // namespace pct
@@ -1422,21 +1471,20 @@ static pct_status emit_common(int32_t n_jobs, const pct_job *jobs, void *ws, siz
     const int32_t *eorder = (const int32_t *)(w + P.L.order_off);
     int32_t *flags = (int32_t *)(w + P.L.flags_off);
     void *rows = w + P.L.rows_off;
-    const dim3 grid((unsigned)T);
     char *rb = (char *)rows;
     WsHeader *hdr = (WsHeader *)w;
     if (mixed) {
         if (!store)
             launch_count<double, false>(P.cdim_base, P.cdim_tiles, s, J, eorder + n_jobs, n_jobs, nullptr, nullptr,
                                         flags, rb);
-        if (store) launch_emit<double, true>(P, has2, has3, s, J, eorder, n_jobs, rb, flags, status, hdr, grid);
-        else launch_emit<double, false>(P, has2, has3, s, J, eorder, n_jobs, rb, flags, status, hdr, grid);
+        if (store) launch_emit<double, true>(P, has2, has3, s, J, eorder, n_jobs, rb, flags, status, hdr);
+        else launch_emit<double, false>(P, has2, has3, s, J, eorder, n_jobs, rb, flags, status, hdr);
     } else {
         if (!store)
             launch_count<float, false>(P.cdim_base, P.cdim_tiles, s, J, eorder + n_jobs, n_jobs, nullptr, nullptr,
                                        flags, rb);
-        if (store) launch_emit<float, true>(P, has2, has3, s, J, eorder, n_jobs, rb, flags, status, hdr, grid);
-        else launch_emit<float, false>(P, has2, has3, s, J, eorder, n_jobs, rb, flags, status, hdr, grid);
+        if (store) launch_emit<float, true>(P, has2, has3, s, J, eorder, n_jobs, rb, flags, status, hdr);
+        else launch_emit<float, false>(P, has2, has3, s, J, eorder, n_jobs, rb, flags, status, hdr);
     }
     return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
 }
