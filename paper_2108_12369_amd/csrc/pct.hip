@@ -372,7 +372,8 @@ template <typename R, bool STORE, int DIM, bool LANES>
 __global__ void __launch_bounds__(TILE, LANES ? 4 : 1)
 k_emit_wave(const JobDev *__restrict__ jobs, const int32_t *__restrict__ eorder, int n_jobs, char *__restrict__ rowbuf,
             const int32_t *__restrict__ tile_flags, int32_t *__restrict__ status, int64_t tile_base, LaneTiles lt) {
-    __shared__ __attribute__((aligned(16))) uint2 stage[TILE / WAVE][STAGE_CAP + 1];   // 1024 slots per wave
+    // 1024 slots per wave, each slice at a multiple of its size (item_fast)
+    __shared__ __attribute__((aligned((STAGE_CAP + 1) * sizeof(uint2)))) uint2 stage[TILE / WAVE][STAGE_CAP + 1];
     const int lane = threadIdx.x % WAVE;
     int64_t tile = tile_base + blockIdx.x;
     if constexpr (LANES) {
@@ -408,7 +409,8 @@ __global__ void __launch_bounds__(TILE) k_emit_queue(const JobDev *__restrict__ 
                                                      int n_jobs, char *__restrict__ rowbuf, int32_t *__restrict__ status,
                                                      unsigned long long *__restrict__ qnext, int64_t tile_base,
                                                      int64_t n_tiles) {
-    __shared__ __attribute__((aligned(16))) uint2 stage[TILE / WAVE][STAGE_CAP + 1];   // 1024 slots per wave
+    // 1024 slots per wave, each slice at a multiple of its size (item_fast)
+    __shared__ __attribute__((aligned((STAGE_CAP + 1) * sizeof(uint2)))) uint2 stage[TILE / WAVE][STAGE_CAP + 1];
     __shared__ int64_t taken;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const int lane = threadIdx.x % WAVE;

@@ -406,14 +406,19 @@ __device__ __forceinline__ void piece_point(const LaneP<R> &p, int m, R mf, R F[
         F[d] = d < DIM ? r_fma<R>(r_fma<R>(r_fma<R>(p.c3[d], t, p.c2[d]), t, p.c1[d]), t, p.c0[d]) : R(0);
 }
 
-// Same, for m >= 1 >= tS (or a piece with tS = tE = 0): the same point as piece_point.
+// The piece's point at t: for t = min(m, tE), m >= 1 >= tS (or a piece with tS = tE = 0),
+// the point piece_point gives for m.
 template <typename R, int DIM>
-__device__ __forceinline__ void piece_next(const LaneP<R> &p, int m, R mf, R F[3]) {
-    (void)m;
-    const R t = r_fmin<R>(mf, p.tE);
+__device__ __forceinline__ void piece_at(const LaneP<R> &p, R t, R F[3]) {
 #pragma unroll
     for (int d = 0; d < 3; ++d)
         F[d] = d < DIM ? r_fma<R>(r_fma<R>(r_fma<R>(p.c3[d], t, p.c2[d]), t, p.c1[d]), t, p.c0[d]) : R(0);
+}
+
+// v kept in [lo, hi] (lo <= hi), as the median of the three: one instruction (v_med3_i32),
+// where min(max(v, lo), hi) takes two, since the compiler cannot know the order of the limits.
+__device__ __forceinline__ int clamp_i32(int v, int lo, int hi) {
+    return max(min(v, lo), min(max(v, lo), hi));
 }
 
 // Voxel of a point and its position in that voxel (voxel units).  The index is kept in
@@ -430,8 +435,7 @@ __device__ __forceinline__ void piece_voxel(const LaneP<R> &p, const R F[3], int
             // truncation equals the floor for F >= 0, and the range starts at 0 or above,
             // so this is the floor clamped into [lo, hi] (a conversion that saturates
             // keeps any F in the range)
-            const int t = (int)F[d];
-            I[d] = min(max(t, p.lo[d]), p.hi[d]);
+            I[d] = clamp_i32((int)F[d], p.lo[d], p.hi[d]);
             fr[d] = F[d] - R(I[d]);
         }
     }
@@ -443,7 +447,7 @@ template <typename R>
 __device__ __forceinline__ int axis_index(const LaneP<R> &p, int d, R mf) {
     const R t = r_fmin<R>(r_fmax<R>(mf, p.tS), p.tE);
     const R F = r_fma<R>(r_fma<R>(r_fma<R>(p.c3[d], t, p.c2[d]), t, p.c1[d]), t, p.c0[d]);
-    return min(max((int)F, p.lo[d]), p.hi[d]);
+    return clamp_i32((int)F, p.lo[d], p.hi[d]);
 }
 
 // Crossings of a ray piece: its voxel indices are monotone over the item ends, so per
@@ -567,6 +571,7 @@ static_assert(rv_bytes<double>() % 16 == 0 && STAGE_ROW_MAX % 2 == 0, "the copy 
 // global_* instructions, counted by vmcnt only (a generic pointer gives flat_*
 // instructions, which every wait for a scalar or LDS access also waits for).
 #define PCT_GLOBAL __attribute__((address_space(1)))
+#define PCT_LDS __attribute__((address_space(3)))
 template <typename T> __device__ __forceinline__ PCT_GLOBAL T *gptr(T *p) { return (PCT_GLOBAL T *)p; }
 
 
@@ -708,37 +713,52 @@ struct Walker {
     int32_t cur;
 };
 
+// State of a lane walking items with at most one crossing per axis.
+struct FastWalk {
+    float head, pend;   // as in Walker
+    uint32_t at, at0;   // byte offset in the wave's slice of the lane's next entry, and of its first
+    int32_t cur;
+};
+
 // Item with at most one crossing per axis.  The displacement and the distance to the
 // face are taken in R from the positions (no cancellation for an item nearly parallel to
 // a face); their ratio -- the crossing's parameter in the item -- and the piece lengths
 // are FP32.  The face distance F - (I + 1) or F - I equals the position in the voxel
 // (F - I, exact) less 1 or 0, bit for bit.  The crossings are ordered by parameter, ties
 // keeping the lower axis.  The item closes up to DIM entries, staged at the lane's next
-// slots (Pc + done ...); a close with no crossing behind it writes the lane's next slot
+// slots; a close with no crossing behind it writes the lane's next slot
 // instead, which a later store of the wave overwrites in program order (this lane's next
 // entry, the head of the next lane with a crossing, or the row's last entry), so every
 // lane stores on every item without a branch.
-template <typename R, int DIM, typename TW>
-__device__ __forceinline__ void item_fast(const float hf[3], const int32_t stride[3], const int Ip[3],
-                                          const R Fp[3], const int Ie[3], const R Fe[3], Walker &wk,
-                                          RowOut<TW> &out, int Pc) {
+// The emit of curved rows is bound by the issue of these instructions, so they are counted:
+// slots kept as byte offsets (one and-or per store; `in`: the slice's offset mask, in a
+// register, `base`: the slice's address, a multiple of its size), the column steps as 24-bit products (a 32-bit one takes four issue
+// slots; setup_row lets no grid with a stride of 2^23 or more in here) and the number of
+// crossings as a sum of squares.  This and
+// the item ends of wave_row took an item from 77 to 70 (2D) and from 120 to 108 VALU (3D):
+// 100,003 curved 3D rows without A 266 -> 257 us, 1M on 200 x 200 x 160 2.19 -> 2.14 ms,
+// 2.95M on 400 x 400 6.15 -> 6.03 ms (the waves wait longer on memory instead).
+template <typename R, int DIM>
+__device__ __forceinline__ void item_fast(const float hf[3], const int32_t stride[3], const int Ip[3], const R Fp[3],
+                                          const int Ie[3], const R Fe[3], FastWalk &wk, uint32_t in, uint32_t base) {
     float lam[3] = {2.f, 2.f, 2.f}, dn2 = 0.f;
     int32_t dc[3] = {0, 0, 0};
-    int tot = 0;
+    uint32_t tot = 0;
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
         const int di = Ie[d] - Ip[d];   // -1, 0 or 1
         const float dff = (float)(Fe[d] - Fp[d]);
         const float dm = dff * hf[d];
         dn2 = fmaf(dm, dm, dn2);
-        // distance to the face crossed, in R and rounded once: near a face its absolute
-        // error must stay small, since a chord nearly parallel to the face divides it by a
-        // small displacement
-        const float dist = (float)(Fp[d] - R(Ip[d] + (di > 0 ? 1 : 0)));
+        // distance to the face crossed (the upper index of the two), in R and rounded once:
+        // near a face its absolute error must stay small, since a chord nearly parallel to
+        // the face divides it by a small displacement
+        const float dist = (float)(Fp[d] - R((int)max((uint32_t)Ie[d], (uint32_t)Ip[d])));
         // in [0, 1] (a NaN from a vanishing displacement becomes 1: the item's end)
-        lam[d] = di != 0 ? fminf(fabsf(dist) * __builtin_amdgcn_rcpf(fabsf(dff)), 1.f) : 2.f;
-        dc[d] = di * stride[d];
-        tot += di != 0 ? 1 : 0;
+        const float l = fminf(fabsf(dist) * __builtin_amdgcn_rcpf(fabsf(dff)), 1.f);
+        lam[d] = di != 0 ? l : 2.f;
+        dc[d] = d == 0 ? di : __mul24(di, stride[d]);
+        tot += (uint32_t)__mul24(di, di);
     }
     const float len = __builtin_amdgcn_sqrtf(dn2);
     // parameters in order, and the column steps of the first and the last crossing axis
@@ -760,18 +780,23 @@ __device__ __forceinline__ void item_fast(const float hf[3], const int32_t strid
         dlast = c10 ? dc[0] : dc[1];
     }
     const int32_t dsum = DIM == 3 ? dc[0] + dc[1] + dc[2] : dc[0] + dc[1];
-    const int base = wk.done, slot = Pc + base;
+    // entry at byte offset `at` of the slice; the mask keeps even an inconsistent row inside
+    auto put = [&](uint32_t at, int32_t col, float l) {
+        PCT_LDS uint2 *const e = (PCT_LDS uint2 *)(uintptr_t)((at & in) | base);
+        e->x = (uint32_t)col;
+        e->y = __float_as_uint(l);
+    };
     // first crossing: closes the entry open at the item's start
     const float len0 = fmaf(l0, len, wk.pend);
-    wk.head = (base == 0 && tot > 0) ? len0 : wk.head;   // the lane's first entry
-    out.put(slot, wk.cur, len0);
+    wk.head = wk.at == wk.at0 ? len0 : wk.head;   // the lane's first entry (without a crossing yet: set again)
+    put(wk.at, wk.cur, len0);
     const int32_t cur1 = wk.cur + dfirst;
-    out.put(slot + (tot < 1 ? tot : 1), cur1, (l1 - l0) * len);   // second crossing
+    put(wk.at + (tot == 0 ? 0u : 8u), cur1, (l1 - l0) * len);   // second crossing
     if (DIM == 3)   // third crossing
-        out.put(slot + (tot < 2 ? tot : 2), cur1 + dsum - dfirst - dlast, (l2 - l1) * len);
+        put(wk.at + 8u * min(tot, 2u), wk.cur + dsum - dlast, (l2 - l1) * len);
     const float lp = DIM == 3 && tot > 2 ? l2 : (tot > 1 ? l1 : (tot > 0 ? l0 : 0.f));
     wk.cur += dsum;
-    wk.done = base + tot;
+    wk.at += 8u * tot;
     wk.pend = (tot == 0 ? wk.pend : 0.f) + (1.f - lp) * len;
 }
 
@@ -1027,24 +1052,30 @@ __device__ __forceinline__ void wave_row(const JobDev &J, LdsRow wl, int kind, R
             }
             Lt = sqrtf(l2);
         }
+        FastWalk fw{0.f, 0.f, (uint32_t)Pc * 8u, (uint32_t)Pc * 8u, wk.cur};
+        const uint32_t sbase = (uint32_t)(uintptr_t)(PCT_LDS uint2 *)out.stage;
+        uint32_t slice = (STAGE_CAP + 1) * 8 - 1;
+        asm volatile("" : "+v"(slice));   // kept in a register
+        // item ends: m = first + 1, first + 2, ... up to last, at t = min(m, tE)
+        R mf = R(first);
+        const R tcap = r_fmin<R>(R(last), P.tE);
 #pragma unroll 2
         for (int it = 0; it < K; ++it) {
-            const int m = min(first + it + 1, last);   // item end
-            const R mf = R(m);
+            mf += R(1);
+            const R t = r_fmin<R>(mf, tcap);
             R Fe[3], fre[3];
             int Ie[3];
             if (RAY) {
                 // linear item ends: F(t) = c0 + c1 t
-                const R t = r_fmin<R>(mf, P.tE);
 #pragma unroll
                 for (int d = 0; d < 3; ++d) Fe[d] = d < DIM ? r_fma<R>(P.c1[d], t, P.c0[d]) : R(0);
                 piece_voxel<R, DIM>(P, Fe, Ie, fre);
                 item_ray<R, DIM>(inv_rate, Lt, (float)(t - tp), stride, Ip, frp, Ie, wk, close);
                 tp = t;
             } else {
-                piece_next<R, DIM>(P, m, mf, Fe);
+                piece_at<R, DIM>(P, t, Fe);
                 piece_voxel<R, DIM>(P, Fe, Ie, fre);
-                if (FAST) item_fast<R, DIM>(hf, stride, Ip, Fp, Ie, Fe, wk, out, Pc);
+                if (FAST) item_fast<R, DIM>(hf, stride, Ip, Fp, Ie, Fe, fw, slice, sbase);
                 else item_general<R, DIM>(hf, stride, Ip, Fp, frp, Ie, Fe, wk, close);
             }
 #pragma unroll
@@ -1054,6 +1085,7 @@ __device__ __forceinline__ void wave_row(const JobDev &J, LdsRow wl, int kind, R
                 frp[d] = fre[d];
             }
         }
+        if (FAST && !RAY) wk = Walker{fw.head, fw.pend, (int)(fw.at - fw.at0) / 8, fw.cur};
         // a lane past the pieces walked a point that need not exist: nothing of it is kept
         if (!has_items) wk.pend = 0.f;
     }
@@ -1229,7 +1261,8 @@ __device__ __forceinline__ RowSetup setup_row(const JobDev &J, int64_t g, RowRef
     if (J.path == 1) make_path<R, DIM, true>(J, g, p);
     else make_path<R, DIM, false>(J, g, p);
     const R ninf = -r_inf<R>(), pinf = r_inf<R>();
-    int kind = 0, fast = 1;   // fast: every item crosses each axis at most once
+    // fast: every item crosses each axis at most once (and item_fast's column steps hold)
+    int kind = 0, fast = (DIM == 3 ? (int64_t)J.n[0] * J.n[1] : (int64_t)J.n[0]) < (1 << 23) ? 1 : 0;
     int64_t cross = 0;        // face crossings of the pieces
     bool any = false;         // a piece with items
     RV(w, spl.N) = 0;
