@@ -20,9 +20,9 @@
 // level (k_sap_levels): the same updates of every component of y in the same order, so the
 // result is the one of the rows taken one after another, bit for bit.  Measured per
 // iteration, 100 strings: 640,000 rows of the paper's 200 x 160 system 3.20 -> 0.67 ms
-// (one row at a time before), 368,640 curved rows on 400 x 400 5.85 -> 4.43 ms; with the
-// rows in a random order (nearly every pair shares a column) 2.95 -> 1.57 and 5.93 ->
-// 5.29 ms, since the loads and waits of the other rows leave the chain.
+// (one row at a time before), 368,640 curved rows on 400 x 400 5.85 -> 2.42 ms; with the
+// rows in a random order (nearly every pair shares a column) 2.95 -> 1.54 and 5.93 ->
+// 3.91 ms, since the loads and waits of the other rows leave the chain.
 //
 // LDS iterate: the metadata of 64 batches lies in the lanes of each wave, and the first 384
 // entries of its next two rows are always in flight.  A row is projected with only as many
@@ -35,6 +35,9 @@
 // slots; the waves meet at a workgroup barrier once per level.  A row whose columns
 // are distinct (the prepare pass marks the others) is written back with plain stores,
 // which stay in the XCD's L2 for the next row's gathers; global atomic adds would not.
+// With several rows at a time the cache lines that a gather or a scattered store touches are
+// the limit, not the waits, so y is kept in strips of the grid (YOrder): 4.42 -> 2.42 ms per
+// iteration of the 400 x 400 system.
 // The staged entries' gathers and stores go through a buffer resource over y: an entry
 // past the row gets an offset outside it (the load returns 0, the store is dropped), so
 // each chunk is one instruction with no branch around it.
@@ -78,6 +81,28 @@ SapLayout sap_layout(int64_t m, int32_t n, int32_t M) {
     return L;
 }
 
+// Order of a string's y in the workspace.  Columns of a grid of rows of s voxels go in strips
+// of 8 grid rows, each stored by 8-voxel columns: a 128-byte line then holds a patch of 4 x 8
+// voxels, which a path leaves after some 6 entries, where a line of 32 voxels of one grid row
+// serves a steep path once.  The columns from `full` on (a multiple of 8 s) keep their place;
+// full = 0: every column does.  Division by s: c / s = mulhi(c, magic) >> shift, exact for
+// c < 2^29 (magic = ceil(2^(32 + shift) / s), 2^shift < s <= 2^(shift + 1)).
+struct YOrder {
+    uint32_t s, full, magic, shift;
+};
+
+__device__ __forceinline__ uint32_t by_s(const YOrder &o, uint32_t c) { return __umulhi(c, o.magic) >> o.shift; }
+// place of column c
+__device__ __forceinline__ uint32_t y_place(const YOrder &o, uint32_t c) {
+    const uint32_t q = by_s(o, c), ix = c - q * o.s, r = q & 7u;
+    return c < o.full ? c + 7u * ix + r - r * o.s : c;
+}
+// column at place i
+__device__ __forceinline__ uint32_t y_column(const YOrder &o, uint32_t i) {
+    const uint32_t strip = by_s(o, i >> 3), ix = (i >> 3) - strip * o.s;
+    return i < o.full ? (8u * strip + (i & 7u)) * o.s + ix : i;
+}
+
 struct SapArgs {
     int64_t m, nnz;
     int32_t n, M;
@@ -89,7 +114,18 @@ struct SapArgs {
     float *coef;
     uint8_t *lev;   // per position: its level in its batch | (levels of the batch - 1) << 4
     int32_t *status;
+    uint32_t *row_len;   // in the workspace header (k_sap_row_length)
 };
+
+// The order of y for the row length that the prepare pass found (0: every column keeps its
+// place).
+__device__ __forceinline__ YOrder y_order(const SapArgs &a) {
+    const uint32_t s = *a.row_len;
+    if (s < 2 || s > (uint32_t)a.n / 8) return YOrder{1, 0, 0, 0};
+    YOrder o{s, (uint32_t)a.n / (8 * s) * (8 * s), 0, 31u - (uint32_t)__builtin_clz(s - 1)};
+    o.magic = (uint32_t)(((1ull << (32 + o.shift)) + s - 1) / s);
+    return o;
+}
 
 template <typename VT> __device__ __forceinline__ float val_at(const void *v, int64_t e);
 template <> __device__ __forceinline__ float val_at<float>(const void *v, int64_t e) {
@@ -588,8 +624,8 @@ __device__ __forceinline__ void yb_store(__amdgpu_buffer_rsrc_t r, uint32_t off,
 // One staged row projected onto y in the workspace (cf: its signed coefficient).  Its
 // updates are complete when it returns.
 template <typename VT>
-__device__ __forceinline__ void project_ws(const SapArgs &a, float *y, __amdgpu_buffer_rsrc_t yr, uint32_t nu,
-                                           const int32_t *sc, const float *sv, int64_t beg, int64_t end, float b,
+__device__ __forceinline__ void project_ws(const SapArgs &a, const YOrder &o, float *y, __amdgpu_buffer_rsrc_t yr,
+                                           uint32_t nu, const int32_t *sc, const float *sv, int64_t beg, int64_t end, float b,
                                            float cf, int lane) {
     constexpr int PF = Ring<false>::PF, SLOT = PF * 64;
     if (cf == 0.0f) return;
@@ -613,7 +649,7 @@ __device__ __forceinline__ void project_ws(const SapArgs &a, float *y, __amdgpu_
     for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
         const int32_t c = a.cols[e];
         const bool okc = (uint32_t)c < nu;
-        const float yc = ws_load(y, okc ? c : 0);
+        const float yc = ws_load(y, okc ? (int32_t)y_place(o, c) : 0);
         acc = fma(okc ? (double)val_at<VT>(a.vals, e) : 0.0, (double)yc, acc);
     }
     const double dot = wave_sum(acc);
@@ -624,14 +660,14 @@ __device__ __forceinline__ void project_ws(const SapArgs &a, float *y, __amdgpu_
             if (ok[q]) ws_add(y, cc[q], alpha * cv[q]);
         for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
             const int32_t c = a.cols[e];
-            if ((uint32_t)c < nu) ws_add(y, c, alpha * val_at<VT>(a.vals, e));
+            if ((uint32_t)c < nu) ws_add(y, (int32_t)y_place(o, c), alpha * val_at<VT>(a.vals, e));
         }
     } else {
 #pragma unroll
         for (int q = 0; q < PF; ++q) yb_store(yr, ok[q] ? (uint32_t)cc[q] * 4u : Y_OUT, yv[q] + alpha * cv[q]);
         for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
-            const int32_t c = a.cols[e];
-            if ((uint32_t)c < nu) ws_put(y, c, ws_load(y, c) + alpha * val_at<VT>(a.vals, e));
+            const int32_t c = a.cols[e], p = (int32_t)y_place(o, c);
+            if ((uint32_t)c < nu) ws_put(y, p, ws_load(y, p) + alpha * val_at<VT>(a.vals, e));
         }
     }
     ws_settle();
@@ -649,7 +685,8 @@ __global__ __launch_bounds__(128 * SAP_W_WS) void k_sap_string_ws(SapArgs a, con
     const int t = blockIdx.x;
     const int n = a.n;
     float *y = Y + (size_t)t * (size_t)n;
-    for (int j = threadIdx.x; j < n; j += 128 * W) y[j] = x[j];
+    const YOrder o = y_order(a);
+    for (int j = threadIdx.x; j < n; j += 128 * W) y[j] = x[y_column(o, j)];
     __syncthreads();   // (global and LDS) the copy is in L2 before the first gathers
     if (a.nnz == 0) return;   // every row empty (all waves leave here)
 
@@ -683,7 +720,7 @@ __global__ __launch_bounds__(128 * SAP_W_WS) void k_sap_string_ws(SapArgs a, con
                     const RowMeta r = meta_at(A, j0 + j);
 #pragma unroll
                     for (int q = 0; q < PF; ++q) {
-                        sc[slot][w][q * 64 + lane] = cq[j][q];
+                        sc[slot][w][q * 64 + lane] = (int32_t)y_place(o, (uint32_t)cq[j][q]);
                         sv[slot][w][q * 64 + lane] = widen(vq[j][q]);
                     }
                     if (lane == 0) {
@@ -713,7 +750,7 @@ __global__ __launch_bounds__(128 * SAP_W_WS) void k_sap_string_ws(SapArgs a, con
                 const int slot = j & 1;   // batch k0 + j, k0 even
                 const int mine = __builtin_amdgcn_readlane(A.mine, j), top = __builtin_amdgcn_readlane(A.top, j);
                 for (int l = 0; l <= top; ++l) {
-                    if (l == mine) project_ws<VT>(a, y, yr, nu, sc[slot][w], sv[slot][w], sbeg[slot][w], send[slot][w],
+                    if (l == mine) project_ws<VT>(a, o, y, yr, nu, sc[slot][w], sv[slot][w], sbeg[slot][w], send[slot][w],
                                                   sb[slot][w], scoef[slot][w], lane);
                     // the next level's gathers, by any wave, see this level's updates
                     lds_barrier();
@@ -725,12 +762,48 @@ __global__ __launch_bounds__(128 * SAP_W_WS) void k_sap_string_ws(SapArgs a, con
     }
 }
 
-__global__ void k_sap_average(const float *Y, const double *w, int32_t M, int32_t n, float *x) {
+// STRIPS: y in the order of the workspace iterate.
+template <bool STRIPS>
+__global__ void k_sap_average(SapArgs a, const float *Y, const double *w, int32_t M, int32_t n, float *x) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
     double s = 0.0;
+#pragma unroll 8
     for (int32_t t = 0; t < M; ++t) s = fma(w[t], (double)Y[(size_t)t * (size_t)n + (size_t)j], s);
-    x[j] = (float)s;
+    x[STRIPS ? y_column(y_order(a), (uint32_t)j) : (uint32_t)j] = (float)s;
+}
+
+// The row length s of the grid the columns come from: consecutive entries of a path lie in
+// neighbouring voxels, so their columns differ by 1 or s (or a plane).  The most frequent
+// difference above 1 of 8,192 pairs spread over the entries, if an eighth of them show it and
+// 8 rows of s fit n; else the columns keep their places.  Any s is correct.
+constexpr int LEN_PAIRS = 8192, LEN_SLOTS = 2048, LEN_THREADS = 1024;
+__global__ __launch_bounds__(LEN_THREADS) void k_sap_row_length(SapArgs a) {
+    __shared__ uint32_t key[LEN_SLOTS], num[LEN_SLOTS];
+    __shared__ unsigned long long best;
+    for (int j = threadIdx.x; j < LEN_SLOTS; j += LEN_THREADS) key[j] = num[j] = 0u;
+    if (threadIdx.x == 0) best = 0ull;
+    __syncthreads();
+    const int64_t pairs = a.nnz - 1 < LEN_PAIRS ? a.nnz - 1 : LEN_PAIRS;
+    for (int64_t k = threadIdx.x; k < pairs; k += LEN_THREADS) {
+        const int64_t e = (int64_t)((double)k * ((double)(a.nnz - 1) / (double)pairs));   // < nnz - 1
+        int64_t d = (int64_t)a.cols[e + 1] - a.cols[e];
+        d = d < 0 ? -d : d;
+        if (d < 2 || d > a.n / 8) continue;
+        uint32_t h = ((uint32_t)d * 2654435761u) >> 21;
+        for (int step = 0; step < 16; ++step, h = (h + 1) & (LEN_SLOTS - 1)) {
+            const uint32_t was = atomicCAS(&key[h], 0u, (uint32_t)d);
+            if (was == 0u || was == (uint32_t)d) {
+                atomicAdd(&num[h], 1u);
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    for (int j = threadIdx.x; j < LEN_SLOTS; j += LEN_THREADS)
+        atomicMax(&best, ((unsigned long long)num[j] << 32) | key[j]);
+    __syncthreads();
+    if (threadIdx.x == 0) *a.row_len = (best >> 32) * 8 >= (unsigned long long)pairs ? (uint32_t)best : 0u;
 }
 
 __global__ void k_sap_uniform(double *w, int32_t M) {
@@ -784,6 +857,7 @@ SapArgs make_args(const pct_csr *A, const pct_sap *p, char *ws, const SapLayout 
     a.coef = (float *)(ws + L.coef_off);
     a.lev = (uint8_t *)(ws + L.lev_off);
     a.status = (int32_t *)ws;
+    a.row_len = (uint32_t *)(ws + 64);
     return a;
 }
 
@@ -901,6 +975,7 @@ pct_status pct_sap_prepare(const pct_csr *A, const pct_sap *p, void *ws_dev, siz
                                p->relax);
         }
     }
+    if (!y_in_lds(A->n_cols) && A->nnz > 0) hipLaunchKernelGGL(k_sap_row_length, dim3(1), dim3(LEN_THREADS), 0, s, a);
     if (hipGetLastError() != hipSuccess) return PCT_EHIP;
     return p->order_dev ? PCT_OK : launch_levels(a, s);
 }
@@ -929,7 +1004,12 @@ pct_status pct_sap_iterate(const pct_csr *A, const pct_sap *p, float *x_dev, int
         const pct_status ls = A->val_dtype == PCT_F16 ? launch_strings<__half>(a, x_dev, Y, s)
                                                       : launch_strings<float>(a, x_dev, Y, s);
         if (ls != PCT_OK) return ls;
-        hipLaunchKernelGGL(k_sap_average, dim3(avg_blocks), dim3(256), 0, s, Y, w, p->n_strings, A->n_cols, x_dev);
+        if (y_in_lds(A->n_cols))
+            hipLaunchKernelGGL((k_sap_average<false>), dim3(avg_blocks), dim3(256), 0, s, a, Y, w, p->n_strings, A->n_cols,
+                               x_dev);
+        else
+            hipLaunchKernelGGL((k_sap_average<true>), dim3(avg_blocks), dim3(256), 0, s, a, Y, w, p->n_strings, A->n_cols,
+                               x_dev);
         if (hipGetLastError() != hipSuccess) return PCT_EHIP;
     }
     return PCT_OK;

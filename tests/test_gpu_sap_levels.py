@@ -81,3 +81,30 @@ def test_order_buffer_changed_between_iterations(P, oracle, n):
                           n_iter=1, n_strings=3, relax=0.9, order=o)
     err = float(np.abs(x.cpu().numpy() - want).max())
     assert err <= 1e-5 * float(np.abs(want).max()) + 1e-6, err
+
+
+# y in strips of the grid the columns come from: the row length found among the entries
+# (8 grid rows fit n, or not; the last strip cut off by n), several candidates, none
+@pytest.mark.parametrize("n,s", [(40904, 5113), (40904, 5114), (50000, 250), (50001, 333), (65536, 2), (50000, 1)])
+def test_strip_order(P, oracle, n, s):
+    m = 400
+    rng = np.random.default_rng(n + s)
+    rp, cols = [0], []
+    for i in range(m):
+        k = int(rng.integers(1, 900))
+        c = int(rng.integers(0, n)) + np.cumsum(np.where(rng.uniform(size=k) < 0.5, 1, s) * (1 if i % 2 else -1))
+        c = np.unique(c[(c >= 0) & (c < n)])
+        cols.append(c)
+        rp.append(rp[-1] + len(c))
+    rp, cols = np.asarray(rp, np.int64), np.concatenate(cols).astype(np.int32)
+    vals = rng.uniform(0.05, 2.0, int(rp[-1])).astype(np.float32)
+    xt = rng.uniform(0.0, 1.5, n)
+    b = np.bincount(np.repeat(np.arange(m), np.diff(rp)), vals.astype(np.float64) * xt[cols], minlength=m).astype(np.float32)
+    S = P.Sap(*(torch.as_tensor(v, device="cuda") for v in (rp, cols, vals, b)), n, n_strings=7, relax=0.8)
+    x = torch.zeros(n, device="cuda")
+    S.iterate(x, 2)
+    assert S.status() == 0
+    want = oracle.sap(rp, cols, vals.astype(np.float64), b.astype(np.float64), n, np.zeros(n), n_iter=2, n_strings=7,
+                      relax=0.8)
+    err = float(np.abs(x.cpu().numpy() - want).max())
+    assert err <= 1e-5 * float(np.abs(want).max()) + 1e-6, err
