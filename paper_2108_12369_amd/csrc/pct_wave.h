@@ -578,6 +578,22 @@ template <typename T> __device__ __forceinline__ PCT_GLOBAL T *gptr(T *p) { retu
 // Bit offsets of y and z in the packed voxel coordinates of a staged entry (stage_strides).
 constexpr int PACK_Y = 10, PACK_Z = 21;
 
+// a b + c of 24-bit operands, unsigned (b uniform) and signed: one full-rate instruction each,
+// for which the compiler, where it cannot bound b, takes a 64-bit multiply-add of four slots.
+// (The copy-out of packed coordinates with them and fewer steps, about 34 -> 21 issue slots per
+// 64 entries: 1M curved 3D rows 2.14 -> 2.08 ms, 5M 9.72 -> 9.45 ms, 640,000 straight 2D rows
+// 0.558 -> 0.540 ms, 300,001 straight 3D rows 0.335 -> 0.323 ms.)
+__device__ __forceinline__ uint32_t mad24u(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ uint32_t mad24s(uint32_t a, int32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
+    return r;
+}
+
 template <typename TW>
 struct RowOut {
     PCT_GLOBAL int32_t *cols;
@@ -586,7 +602,8 @@ struct RowOut {
     PCT_GLOBAL const float *x;
     PCT_GLOBAL const float *xb;   // the bricked copy of x (staged entries hold packed
     bool pack;                    // coordinates); gn: grid sizes, nbx, nby: bricks per
-    uint32_t gn[3], nbx, nby;     // grid row and per plane
+    uint32_t gn[3], nbx, nby;     // grid row and per plane; nxb: elements of the copy
+    uint32_t nxb;
     uint2 *stage;   // the wave's LDS slice
     uint32_t nvox;  // size of x: every gather index is kept below it
     int32_t len;
@@ -623,17 +640,16 @@ struct RowOut {
     }
     // Write the n staged entries and add their share of b.  Lanes take consecutive
     // entries (neighbouring voxels along the path share the cache lines of x), in groups
-    // of 256 without branches inside a group: all LDS reads, then all gathers (an entry
+    // of 64 G without branches inside a group: all LDS reads, then all gathers (an entry
     // past the row reads x[0], one cache line for all of them, and counts 0), then the
     // stores, so that each kind of access is in flight together.  With packed coordinates
-    // (PACK) the column and the brick address are computed from them; an entry whose
-    // coordinates lie outside the grid reads element 0 of the copy.
-    template <bool WB, bool HALF, bool PACK>
+    // (PACK) the column and the brick address are computed from them; an address outside
+    // the copy reads element 0.
+    template <bool WB, bool HALF, bool PACK, int G>   // G chunks of 64 entries per group
     __device__ __forceinline__ void flush_t(int n, int lane) {
-        constexpr int G = 4;   // chunks of 64 entries per group
         n = n < STAGE_CAP + 1 ? n : STAGE_CAP + 1;
         const int m = store ? (n < len ? n : len) : 0;   // entries stored
-        const bool cst = chord > 0.f;
+        const float scale = chord > 0.f ? 0.f : 1.f;
         __builtin_amdgcn_wave_barrier();
         // the wave's output phase runs at a raised issue priority, back to 0 once the row's
         // b is stored (emit_rows_wave): its loads and stores go out while the other waves
@@ -649,14 +665,17 @@ struct RowOut {
             for (int u = 0; u < G; ++u) {
                 const int e = g0 + u * WAVE + lane;
                 if (PACK) {
+                    // column ix + n0 (iy + n1 iz); place in the copy 64 brick + 8 ry + rx, the
+                    // brick's number (ix >> 3) + nbx ((iy >> 3) + nby iz), with ix = 8 (ix >> 3)
+                    // + rx and likewise iy: 8 (ix + nbx (iy + 8 nby iz) - (nbx - 1) ry) - 7 rx
+                    // (24-bit operands: ix < 2^10, iy, iz < 2^11, nbx <= 2^7, nby <= 2^8)
                     const uint32_t ix = v[u].x & ((1u << PACK_Y) - 1u);
                     const uint32_t iy = (v[u].x >> PACK_Y) & ((1u << (PACK_Z - PACK_Y)) - 1u);
                     const uint32_t iz = v[u].x >> PACK_Z;
-                    // (24-bit operands: x < 1024, y, z < 2048, bricks per row <= 128)
-                    col[u] = __umul24(gn[0], __umul24(gn[1], iz) + iy) + ix;
-                    const uint32_t brick = __umul24(__umul24(iz, nby) + (iy >> 3), nbx) + (ix >> 3);
-                    const bool in = e < n && ix < gn[0] && iy < gn[1] && iz < gn[2];
-                    xi[u] = in ? (brick << 6) + ((iy & 7u) << 3) + (ix & 7u) : 0u;
+                    col[u] = mad24u(mad24u(iz, gn[1], iy), gn[0], ix);
+                    const uint32_t line = mad24u(mad24u(iz, 8u * nby, iy), nbx, ix);
+                    const uint32_t at = 8u * mad24s(iy & 7u, 1 - (int32_t)nbx, line) - 7u * (ix & 7u);
+                    xi[u] = e < n && at < nxb ? at : 0u;
                 } else {
                     col[u] = v[u].x;
                     xi[u] = (e < n && v[u].x < nvox) ? v[u].x : 0u;
@@ -672,7 +691,7 @@ struct RowOut {
                 const int e = g0 + u * WAVE + lane;
                 if (e < m) {
                     // non-temporal: nothing here reads the output again, and x is kept in L2
-                    const float sv = cst ? chord : __uint_as_float(v[u].y);
+                    const float sv = fmaf(__uint_as_float(v[u].y), scale, chord);   // the length, or the chord
                     __builtin_nontemporal_store((int32_t)col[u], &cols[e]);
                     if (HALF) __builtin_nontemporal_store((uint16_t)__half_as_ushort(__float2half_rn(sv)), &vh[e]);
                     else __builtin_nontemporal_store(sv, &vf[e]);
@@ -688,14 +707,26 @@ struct RowOut {
         }
         __builtin_amdgcn_wave_barrier();
     }
+    // Groups of 3, 4 or 5 chunks, whichever leaves the fewest past the row: a chunk of packed
+    // coordinates costs some 21 VALU whether it holds entries or not.  (Against groups of 4:
+    // 5M curved rows of 307 entries 9.45 -> 9.30 ms, 12 jobs of a batch 7.61 -> 7.49 ms, rows
+    // of 164 entries 0.540 -> 0.536, 300,001 of 154 entries 0.323 -> 0.327.  Columns cost 12 a
+    // chunk, where it gained nothing.)
+    template <bool WB, bool HALF, bool PACK>
+    __device__ __forceinline__ void flush_g(int n, int lane) {
+        const int c = (n + WAVE - 1) / WAVE;
+        if (PACK && (c == 5 || c == 10)) flush_t<WB, HALF, PACK, 5>(n, lane);
+        else if (PACK && (c <= 3 || c == 6 || c == 9)) flush_t<WB, HALF, PACK, 3>(n, lane);
+        else flush_t<WB, HALF, PACK, 4>(n, lane);
+    }
     template <bool PACK>
     __device__ __forceinline__ void flush_p(int n, int lane) {
         if (want_b) {
-            if (half) flush_t<true, true, PACK>(n, lane);
-            else flush_t<true, false, PACK>(n, lane);
+            if (half) flush_g<true, true, PACK>(n, lane);
+            else flush_g<true, false, PACK>(n, lane);
         } else {
-            if (half) flush_t<false, true, PACK>(n, lane);
-            else flush_t<false, false, PACK>(n, lane);
+            if (half) flush_g<false, true, PACK>(n, lane);
+            else flush_g<false, false, PACK>(n, lane);
         }
     }
     // rows of a job with a bricked copy of x hold packed coordinates
@@ -1420,6 +1451,7 @@ __device__ __forceinline__ void emit_rows_wave(const JobDev &J, char *rowbuf, in
         out.gn[2] = (uint32_t)J.n[2];
         out.nbx = (uint32_t)J.nbx;
         out.nby = (uint32_t)J.nby;
+        out.nxb = (uint32_t)J.nbx * (uint32_t)J.nby * (uint32_t)(DIM == 3 ? J.n[2] : 1) * 64u;
         out.wepl = 0.f;
         out.wacc = TW(0);
         out.half = (J.val_dtype == PCT_F16);
