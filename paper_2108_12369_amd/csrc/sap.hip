@@ -7,6 +7,8 @@
 //                                     with a column bitmap in LDS, or a hash table when
 //                                     n is large)
 //                     k_sap_levels    which rows of a string can be projected side by side
+//                     k_sap_prepare_levels  both, where y is in the workspace and the rows
+//                                     are in their natural order
 //   pct_sap_iterate : k_sap_levels    (only when the caller gives a row order)
 //                     k_sap_string    one workgroup per string, y in LDS (when n floats
 //                                     fit): y = x_k, then the relaxed projection of every
@@ -64,6 +66,7 @@ template <> struct Ring<false> { static constexpr int D = 2, PF = 12; };
 // Rows of a string projected side by side (see k_sap_levels), one per wave: y in LDS, and
 // y in the workspace (there each row has a loading and a projecting wave).
 constexpr int SAP_W_LDS = 16, SAP_W_WS = 8;
+constexpr int SAP_NAMES_BITS = 14;   // k_sap_prepare_levels' table: 2^14 words, two blocks per CU
 
 struct SapLayout {
     size_t coef_off, lev_off, w_off, y_off, total;
@@ -178,6 +181,41 @@ __device__ __forceinline__ bool seen_before(unsigned long long *tab, uint32_t ta
     return true;
 }
 
+// The coefficient of row i = [beg, end) from each lane's share of the sum of squares, of the
+// checks and of the repeats found (one wave; dup in any lane: some column repeats).
+template <typename VT>
+__device__ __forceinline__ void store_coef(const SapArgs &a, float relax, int64_t i, int64_t beg, int64_t end, double nrm,
+                                           bool ok, bool dup, int lane) {
+    const bool all_ok = __builtin_amdgcn_ballot_w64(!ok) == 0;
+    const bool repeats = __builtin_amdgcn_ballot_w64(dup) != 0;
+    if (repeats && all_ok) {
+        // ||a_i||^2 of the row as a vector: entries that share a column add into one
+        // component, so the sum over entries e of v_e * (sum of the values of e's
+        // column), which counts each column's (sum of values)^2 once.  Every lane
+        // compares its entries with all of the row's (loads of a uniform index),
+        // quadratic in the row length; rows that repeat a column are few.
+        nrm = 0.0;
+        for (int64_t e0 = beg; e0 < end; e0 += 64) {
+            const int64_t e = e0 + lane;
+            const int32_t ce = e < end ? a.cols[e] : -1;
+            const double ve = e < end ? (double)val_at<VT>(a.vals, e) : 0.0;
+            double s = 0.0;
+            for (int64_t f = beg; f < end; ++f) {
+                const int32_t cf = a.cols[f];
+                const double vf = (double)val_at<VT>(a.vals, f);
+                s += cf == ce ? vf : 0.0;
+            }
+            nrm = fma(ve, s, nrm);
+        }
+    }
+    nrm = wave_sum(nrm);
+    if (lane == 0) {
+        const float cf = (all_ok && nrm > 0.0) ? (float)((double)relax / nrm) : 0.0f;
+        a.coef[i] = repeats ? -cf : cf;
+        if (!all_ok) set_status_dev(a.status, PCT_EINVAL);
+    }
+}
+
 // One wavefront per row: bounds and columns checked, coefficient lambda / ||a_i||^2 in
 // binary64, the norm of the row as a vector of R^n (entries sharing a column summed into
 // one component).  A row that holds some column more than once (a curved path can
@@ -259,34 +297,7 @@ __global__ __launch_bounds__(64 * SAP_WAVES_PREP) void k_sap_prepare(SapArgs a, 
                 __builtin_amdgcn_wave_barrier();
             }
         }
-        const bool all_ok = __builtin_amdgcn_ballot_w64(!ok) == 0;
-        const bool repeats = !hashable || __builtin_amdgcn_ballot_w64(dup) != 0;
-        if (repeats && all_ok) {
-            // ||a_i||^2 of the row as a vector: entries that share a column add into one
-            // component, so the sum over entries e of v_e * (sum of the values of e's
-            // column), which counts each column's (sum of values)^2 once.  Every lane
-            // compares its entries with all of the row's (loads of a uniform index),
-            // quadratic in the row length; rows that repeat a column are few.
-            nrm = 0.0;
-            for (int64_t e0 = beg; e0 < end; e0 += 64) {
-                const int64_t e = e0 + lane;
-                const int32_t ce = e < end ? a.cols[e] : -1;
-                const double ve = e < end ? (double)val_at<VT>(a.vals, e) : 0.0;
-                double s = 0.0;
-                for (int64_t f = beg; f < end; ++f) {
-                    const int32_t cf = a.cols[f];
-                    const double vf = (double)val_at<VT>(a.vals, f);
-                    s += cf == ce ? vf : 0.0;
-                }
-                nrm = fma(ve, s, nrm);
-            }
-        }
-        nrm = wave_sum(nrm);
-        if (lane == 0) {
-            const float cf = (all_ok && nrm > 0.0) ? (float)((double)relax / nrm) : 0.0f;
-            a.coef[i] = repeats ? -cf : cf;
-            if (!all_ok) set_status_dev(a.status, PCT_EINVAL);
-        }
+        store_coef<VT>(a, relax, i, beg, end, nrm, ok, !hashable || dup, lane);
         if (a.order && lane == 0) {
             const int64_t o = a.order[i];
             if (o < 0 || o >= a.m) set_status_dev(a.status, PCT_EINVAL);
@@ -322,6 +333,24 @@ __device__ __forceinline__ RowMeta fetch_meta(const SapArgs &a, int64_t s, int64
 // a beam lie at random offsets of one or two angles: a batch of 16 rows of the paper's
 // 200 x 160 system has 1.7 levels on average, a batch of 8 curved rows on 400 x 400 1.4.
 //
+// A wave: lane r < W holds the rows of the batch that row r shares a column with, as bits;
+// returns row r's byte of a.lev.
+template <int W> __device__ __forceinline__ uint8_t level_byte(uint32_t mine, int lane) {
+    int lv = 0;
+#pragma unroll
+    for (int v = 0; v < W; ++v) {   // lane v's level is final here
+        const int l = __builtin_amdgcn_readlane(lv, v) + 1;
+        if (lane > v && ((mine >> v) & 1u) && l > lv) lv = l;
+    }
+    int top = 0;
+#pragma unroll
+    for (int v = 0; v < W; ++v) {
+        const int l = __builtin_amdgcn_readlane(lv, v);
+        top = l > top ? l : top;
+    }
+    return (uint8_t)(lv | (top << 4));
+}
+
 // One block of W waves per batch, each wave a row.  In LDS a mask of W bits per column
 // (of `span` columns at a time): every row sets its bit at its columns, then reads back
 // the bits of the others there, then clears them.
@@ -380,37 +409,181 @@ __global__ __launch_bounds__(64 * W) void k_sap_levels(SapArgs a, uint32_t span)
         if (lane == 0) conf[wave] = met & MASK;
         __syncthreads();
         if (wave == 0) {
-            const uint32_t mine = lane < W ? conf[lane] : 0u;
-            int lv = 0;
-#pragma unroll
-            for (int v = 0; v < W; ++v) {   // lane v's level is final here
-                const int l = __builtin_amdgcn_readlane(lv, v) + 1;
-                if (lane > v && ((mine >> v) & 1u) && l > lv) lv = l;
-            }
-            int top = 0;
-#pragma unroll
-            for (int v = 0; v < W; ++v) {
-                const int l = __builtin_amdgcn_readlane(lv, v);
-                top = l > top ? l : top;
-            }
-            if (lane < W && p0 + lane < s1) a.lev[p0 + lane] = (uint8_t)(lv | (top << 4));
+            const uint8_t byte = level_byte<W>(lane < W ? conf[lane] : 0u, lane);
+            if (lane < W && p0 + lane < s1) a.lev[p0 + lane] = byte;
         }
         __syncthreads();   // conf is read before the next batch writes it
     }
 }
 
-// The workspace copy of y, which only the string's own workgroup reads and writes
-// (workgroup scope).
-__device__ __forceinline__ float ws_load(float *y, int32_t c) {
-    return __hip_atomic_load(y + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+// k_sap_prepare and k_sap_levels in one pass over A, for the natural order (whose batches hold
+// every row once).  One block per batch, a wave per row.  The rows meet in an LDS table of T
+// words: every entry writes its name (its column's high bits, its row, its place in the row) to
+// the word its column's low bits select, then reads the word back.  An entry that finds its own
+// name is done; one that finds another of the same column has met that row, or its own: the row
+// repeats a column, and the entry is done too, since that one stands for both.  Those that lost
+// write again, and so on until all are done: of any two entries of one column in two rows, the
+// later to be done met the other.  Nothing is cleared, since a word is only read by those that
+// wrote it, and no column is out of the table's range.  The columns and values of the block's
+// next batch are loaded meanwhile, those of its next but one are located.
+//
+// Bound by the barriers of a batch (three and two per further round; two blocks per CU).  100
+// strings of 176M entries in 160,000 columns: k_sap_prepare, whose hash table takes an LDS
+// atomic per entry, 1.53 ms, then k_sap_levels, whose masks go twice over the columns, 0.72;
+// this 0.93.  With masks set and read here instead 1.20.  With 16 rows per batch (y in LDS) it
+// is no faster than the two: 104M entries in 32,000 columns 0.97 and 0.96 ms.
+// The hash table's limit of 1,024 columns per row is not one here: 20,000 rows of 1,283 entries
+// 28.9 -> 0.31 ms (the longer rows had counted as repeating a column).
+template <typename VT>
+__global__ __launch_bounds__(64 * SAP_W_WS, 4) void k_sap_prepare_levels(SapArgs a, float relax) {
+    constexpr int W = SAP_W_WS, U = 8;         // U: chunks of 64 entries of the row kept in registers
+    constexpr uint32_t LOG_T = SAP_NAMES_BITS, T = 1u << LOG_T, ALL = (1u << W) - 1u;
+    constexpr int MAX_LEN = 64 * 64;           // entries of a row that the lanes' 64-bit masks follow
+    // a name: 16 high bits for the column (below 2^29), 4 for the row, 12 for the place
+    static_assert(W <= 16 && MAX_LEN <= 1 << 12 && LOG_T >= 13, "a name fits a word");
+    extern __shared__ uint32_t tab[];
+    __shared__ uint32_t conf[W];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t n = (uint32_t)a.n;
+    if (threadIdx.x < W) conf[threadIdx.x] = 0u;
+    const int64_t longest = (a.m + a.M - 1) / a.M, per = (longest + W - 1) / W, batches = per * a.M;
+
+    struct Batch {
+        int64_t p0, s1;      // first position, end of the string
+        int64_t beg, end;    // the wave's row
+        int32_t c[U];
+        typename RawOf<VT>::T v[U];
+    };
+    auto locate = [&](Batch &b, int64_t q) {   // where batch q and the wave's row of it lie
+        const int64_t t = q < batches ? q / per : 0;
+        b.p0 = t * a.m / a.M + (q - t * per) * W;
+        b.s1 = q < batches ? (t + 1) * a.m / a.M : 0;
+        b.beg = b.end = 0;
+        if (b.p0 + wave < b.s1) {
+            b.beg = a.row_ptr[b.p0 + wave];
+            b.end = a.row_ptr[b.p0 + wave + 1];
+        }
+    };
+    auto sound = [&](const Batch &b) { return b.beg >= 0 && b.end >= b.beg && b.end <= a.nnz; };
+    auto load = [&](Batch &b) {
+        const bool ok = sound(b);
+        const int64_t len = ok ? b.end - b.beg : 0;
+        const int32_t *cb = a.cols + (ok ? b.beg : 0);
+        const void *vb = (const char *)a.vals + (ok ? b.beg : 0) * (int64_t)sizeof(VT);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = u * 64 + lane;
+            b.c[u] = e < len ? cb[e] : -1;
+            b.v[u] = e < len ? raw_at<VT>(vb, e) : typename RawOf<VT>::T(0);
+        }
+    };
+    auto process = [&](const Batch &b) {
+        bool ok = sound(b);
+        const int64_t len = ok ? b.end - b.beg : 0;
+        const bool huge = len > MAX_LEN;                       // taken to meet every row and itself
+        const int chunks = huge ? 0 : (int)((len + 63) / 64);  // uniform in the wave
+        const int32_t *cols = a.cols + (ok ? b.beg : 0);
+        uint32_t met = 0u;
+        bool dup = huge;
+        uint64_t todo = 0;   // bit u: chunk u's entry is still to be done (a column outside [0, n) is not)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (!huge && (uint32_t)b.c[u] < n) todo |= 1ull << u;
+        for (int u = U; u < chunks; ++u) {
+            const int e = u * 64 + lane;
+            if (e < len && (uint32_t)cols[e] < n) todo |= 1ull << u;
+        }
+        auto name = [&](int32_t c, int u) {
+            return ((uint32_t)c >> LOG_T) << 16 | (uint32_t)wave << 12 | (uint32_t)(u * 64 + lane);
+        };
+        auto check = [&](int32_t c, int u) {
+            const uint32_t v = tab[(uint32_t)c & (T - 1)], own = name(c, u);
+            bool done = v == own;
+            if (!done && (v ^ own) >> 16 == 0) {
+                const uint32_t r = (v >> 12) & 15u;
+                done = r == (uint32_t)wave;
+                dup = dup || done;
+                met |= 1u << r;
+            }
+            if (done) todo &= ~(1ull << u);
+        };
+        do {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if ((todo >> u) & 1) tab[(uint32_t)b.c[u] & (T - 1)] = name(b.c[u], u);
+            for (int u = U; u < chunks; ++u)
+                if ((todo >> u) & 1) tab[(uint32_t)cols[u * 64 + lane] & (T - 1)] = name(cols[u * 64 + lane], u);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if ((todo >> u) & 1) check(b.c[u], u);
+            for (int u = U; u < chunks; ++u)
+                if ((todo >> u) & 1) check(cols[u * 64 + lane], u);
+        } while (__syncthreads_or(todo != 0));   // one entry of every contested word is done each time
+        for (int off = 32; off > 0; off >>= 1) met |= __shfl_xor(met, off, 64);
+        if (huge) met = ALL;
+        // a conflict is the later row's: lane r tells row r of this one, lane `wave` keeps its own
+        if (lane < W) {
+            const uint32_t mine = lane == wave ? met & ((1u << wave) - 1u)
+                                               : (lane > wave && ((met >> lane) & 1u) ? 1u << wave : 0u);
+            if (mine != 0u) atomicOr(&conf[lane], mine);
+        }
+        if (b.p0 + wave < b.s1) {
+            double nrm = 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const double v = (double)widen(b.v[u]);
+                nrm = fma(v, v, nrm);
+                ok = ok && ((uint32_t)b.c[u] < n || u * 64 + lane >= b.end - b.beg);
+            }
+            for (int64_t e = U * 64 + lane; e < len; e += 64) {
+                const double v = (double)val_at<VT>(a.vals, b.beg + e);
+                nrm = fma(v, v, nrm);
+                ok = ok && (uint32_t)cols[e] < n;
+            }
+            store_coef<VT>(a, relax, b.p0 + wave, b.beg, b.end, nrm, ok, dup, lane);
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const uint32_t mine = lane < W ? conf[lane] : 0u;
+            if (lane < W) conf[lane] = 0u;   // (the next batch writes it after its barriers)
+            const uint8_t byte = level_byte<W>(mine, lane);
+            if (lane < W && b.p0 + lane < b.s1) a.lev[b.p0 + lane] = byte;
+        }
+    };
+    // batches q, q + g, ...: the one being processed, the next one's entries in flight, the
+    // one after that located
+    const int64_t g = gridDim.x;
+    int64_t q = blockIdx.x;
+    Batch A, B;
+    locate(A, q);
+    load(A);
+    locate(B, q + g);
+    while (q < batches) {   // the same for the whole block
+        load(B);
+        Batch C;
+        locate(C, q + 2 * g);
+        process(A);
+        q += g;
+        if (q >= batches) break;
+        A.p0 = C.p0;
+        A.s1 = C.s1;
+        A.beg = C.beg;
+        A.end = C.end;
+        load(A);
+        locate(C, q + 2 * g);
+        process(B);
+        q += g;
+        B.p0 = C.p0;
+        B.s1 = C.s1;
+        B.beg = C.beg;
+        B.end = C.end;
+    }
 }
-// Workspace update of a row whose columns are distinct: y[c] = y_c + alpha v, the same
-// binary32 arithmetic as the atomic add, as a store (it stays in this XCD's L2, where the
-// next gathers find it; an atomic add makes them go further).
-__device__ __forceinline__ void ws_put(float *y, int32_t c, float v) {
-    __hip_atomic_store(y + c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-// Workspace update of a row that holds some column twice.
+
+// Workspace update of a row that holds some column twice.  (A row whose columns are distinct
+// is written back with stores, which stay in this XCD's L2, where the next gathers find them;
+// an atomic add makes them go further.  The same binary32 arithmetic.)
 __device__ __forceinline__ void ws_add(float *y, int32_t c, float v) { unsafeAtomicAdd(y + c, v); }
 
 // Workspace iterate: the wave's writes (performed in L2) are complete before its next
@@ -646,11 +819,28 @@ __device__ __forceinline__ void project_ws(const SapArgs &a, const YOrder &o, fl
     double acc = 0.0;
 #pragma unroll
     for (int q = 0; q < PF; ++q) acc = fma(ok[q] ? (double)cv[q] : 0.0, (double)yv[q], acc);
-    for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
-        const int32_t c = a.cols[e];
-        const bool okc = (uint32_t)c < nu;
-        const float yc = ws_load(y, okc ? (int32_t)y_place(o, c) : 0);
-        acc = fma(okc ? (double)val_at<VT>(a.vals, e) : 0.0, (double)yc, acc);
+    // the entries past the slot, REST chunks of 64 with their loads in flight together (rows of
+    // 1,283 entries, 1200 x 1200: 2.92 ms per iteration with one chunk at a time, 2.48 so)
+    constexpr int REST = 4;
+    uint32_t rc[REST];   // byte offset of y's component, or out of range
+    float rv[REST], ry[REST];
+    auto fetch_rest = [&](int64_t e0, bool gather) {
+#pragma unroll
+        for (int u = 0; u < REST; ++u) {
+            const int64_t e = e0 + u * 64 + lane;
+            const int32_t c = e < end ? a.cols[e] : -1;
+            rv[u] = e < end ? val_at<VT>(a.vals, e) : 0.0f;
+            rc[u] = (uint32_t)c < nu ? y_place(o, (uint32_t)c) * 4u : Y_OUT;
+        }
+        if (gather) {
+#pragma unroll
+            for (int u = 0; u < REST; ++u) ry[u] = yb_load(yr, rc[u]);
+        }
+    };
+    for (int64_t e0 = beg + SLOT; e0 < end; e0 += 64 * REST) {
+        fetch_rest(e0, true);
+#pragma unroll
+        for (int u = 0; u < REST; ++u) acc = fma(rc[u] != Y_OUT ? (double)rv[u] : 0.0, (double)ry[u], acc);
     }
     const double dot = wave_sum(acc);
     const float alpha = (float)(((double)b - dot) * (double)coef);
@@ -658,16 +848,19 @@ __device__ __forceinline__ void project_ws(const SapArgs &a, const YOrder &o, fl
 #pragma unroll
         for (int q = 0; q < PF; ++q)
             if (ok[q]) ws_add(y, cc[q], alpha * cv[q]);
-        for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
-            const int32_t c = a.cols[e];
-            if ((uint32_t)c < nu) ws_add(y, (int32_t)y_place(o, c), alpha * val_at<VT>(a.vals, e));
+        for (int64_t e0 = beg + SLOT; e0 < end; e0 += 64 * REST) {
+            fetch_rest(e0, false);
+#pragma unroll
+            for (int u = 0; u < REST; ++u)
+                if (rc[u] != Y_OUT) ws_add(y, (int32_t)(rc[u] >> 2), alpha * rv[u]);
         }
     } else {
 #pragma unroll
         for (int q = 0; q < PF; ++q) yb_store(yr, ok[q] ? (uint32_t)cc[q] * 4u : Y_OUT, yv[q] + alpha * cv[q]);
-        for (int64_t e = beg + SLOT + lane; e < end; e += 64) {
-            const int32_t c = a.cols[e], p = (int32_t)y_place(o, c);
-            if ((uint32_t)c < nu) ws_put(y, p, ws_load(y, p) + alpha * val_at<VT>(a.vals, e));
+        for (int64_t e0 = beg + SLOT; e0 < end; e0 += 64 * REST) {
+            fetch_rest(e0, true);
+#pragma unroll
+            for (int u = 0; u < REST; ++u) yb_store(yr, rc[u], ry[u] + alpha * rv[u]);
         }
     }
     ws_settle();
@@ -903,6 +1096,18 @@ pct_status launch_levels(const SapArgs &a, hipStream_t s) {
 }
 
 template <typename VT>
+pct_status launch_prepare_levels(const SapArgs &a, float relax, hipStream_t s) {
+    constexpr int bytes = 4 << SAP_NAMES_BITS;
+    const int64_t per = (longest_string(a) + SAP_W_WS - 1) / SAP_W_WS, batches = per * a.M;
+    const unsigned blocks = (unsigned)(batches < 1024 ? batches : 1024);
+    if (hipFuncSetAttribute((const void *)k_sap_prepare_levels<VT>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) !=
+        hipSuccess)
+        return PCT_EHIP;
+    hipLaunchKernelGGL((k_sap_prepare_levels<VT>), dim3(blocks), dim3(64 * SAP_W_WS), bytes, s, a, relax);
+    return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
+}
+
+template <typename VT>
 pct_status launch_strings(const SapArgs &a, const float *x, float *Y, hipStream_t s) {
     const size_t bytes = ((size_t)a.n + 64) * sizeof(float);
     if (y_in_lds(a.n)) {
@@ -950,7 +1155,14 @@ pct_status pct_sap_prepare(const pct_csr *A, const pct_sap *p, void *ws_dev, siz
     } else {
         hipLaunchKernelGGL(k_sap_uniform, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, w, M);
     }
-    if (A->n_rows > 0) {
+    // One pass for the coefficients and the levels (k_sap_prepare_levels) where y is in the
+    // workspace; strings of fewer rows than two batches leave too many of its waves without one.
+    const bool together = !p->order_dev && A->nnz > 0 && !y_in_lds(A->n_cols) && longest_string(a) >= 2 * SAP_W_WS;
+    if (together) {
+        const pct_status ls = A->val_dtype == PCT_F16 ? launch_prepare_levels<__half>(a, p->relax, s)
+                                                      : launch_prepare_levels<float>(a, p->relax, s);
+        if (ls != PCT_OK) return ls;
+    } else if (A->n_rows > 0) {
         const int64_t blocks64 = (A->n_rows + SAP_WAVES_PREP - 1) / SAP_WAVES_PREP;
         const unsigned blocks = (unsigned)(blocks64 < 65536 ? blocks64 : 65536);
         // a column bitmap per wave when two blocks of them fit a CU's LDS, else the hash
@@ -977,7 +1189,7 @@ pct_status pct_sap_prepare(const pct_csr *A, const pct_sap *p, void *ws_dev, siz
     }
     if (!y_in_lds(A->n_cols) && A->nnz > 0) hipLaunchKernelGGL(k_sap_row_length, dim3(1), dim3(LEN_THREADS), 0, s, a);
     if (hipGetLastError() != hipSuccess) return PCT_EHIP;
-    return p->order_dev ? PCT_OK : launch_levels(a, s);
+    return p->order_dev || together ? PCT_OK : launch_levels(a, s);
 }
 
 pct_status pct_sap_iterate(const pct_csr *A, const pct_sap *p, float *x_dev, int32_t n_iter, void *ws_dev,
