@@ -6,9 +6,11 @@
 //                       k_count             one lane per row -> per-row entry counts,
 //                                           per-tile sums
 //                       k_scan_tiles        exclusive scan of the tile sums, job totals
+//                                           (when SUM_READS is exceeded)
 //                       k_row_ptr           per-tile scan of the counts -> row_ptr
-//   pct_emit_csr      : k_put_jobs, k_emit  one lane per row -> cols, vals, b
-//   pct_wepl          : k_put_jobs, k_emit  (no A stores) -> b
+//   pct_emit_csr      : k_put_jobs          the table, bricked copies of x
+//                       k_emit_wave, k_emit_lane -> cols, vals, b
+//   pct_wepl          : k_put_jobs, k_count, k_emit_wave, k_emit_lane (no A stores) -> b
 #include "../../include/pct.h"
 #include "pct_device.h"
 #include "pct_wave.h"
@@ -91,29 +93,32 @@ static Layout layout_of(int32_t n_jobs, const int64_t *row_counts, const size_t 
 
 // ------------------------------------------------------------------------ kernels
 
-constexpr int JOBS_PER_PACK = 3800 / (int)sizeof(JobDev);
+// Up to JOBS_PER_PACK jobs of a call as kernel arguments, with their share of the two launch
+// orders (emit, count).  Kernel arguments are copied at launch (and into a graph node at
+// capture), so the job table reaches the device without a host buffer that has to outlive
+// the call.
+constexpr int JOBS_PER_PACK = 3800 / (int)(sizeof(JobDev) + 2 * sizeof(int32_t));
+constexpr uint32_t CLEAR_STATUS = 1, CLEAR_QUEUE = 2;
 struct JobPack {
-    int32_t count;
-    int32_t first;
+    int32_t count, first, n_jobs;
+    uint32_t clear;   // header words to reset
+    int32_t order[2][JOBS_PER_PACK];
     JobDev jobs[JOBS_PER_PACK];
 };
 
-// Kernel arguments are copied at launch (and into a graph node at capture), so the
-// job table reaches the device without a host buffer that has to outlive the call.
-// Bricked copy of x for the b gathers of a job (blockIdx.y: the job; jobs without one
+// Bricked copy of x for the b gathers of a job (block b of BRICK_BLOCKS; jobs without one
 // return at once).  Brick (bx, by, z) holds the voxels x in [8 bx, 8 bx + 8) and y in
 // [8 by, 8 by + 8) of plane z, x fastest; the bricks follow x, then y, then z, so that a
 // 128-byte line covers an 8 x 4 patch of a plane.  Voxels past the grid are 0; no gather
 // index reaches them.  The copy has fewer than 2^31 elements (brick_elems).
 constexpr int BRICK_BLOCKS = 512;
-__global__ void __launch_bounds__(256) k_brick(const JobDev *__restrict__ jobs, int32_t job0) {
-    const JobDev &J = jobs[job0 + (int32_t)blockIdx.y];
+__device__ __forceinline__ void fill_bricks(const JobDev &J, uint32_t b) {
     float *xb = J.xb;
     if (!xb) return;
     const uint32_t nbx = (uint32_t)J.nbx, nby = (uint32_t)J.nby, n0 = (uint32_t)J.n[0], n1 = (uint32_t)J.n[1];
     const uint32_t total = nbx * nby * (uint32_t)J.n[2] * 64u;
     const float *x = J.x;
-    for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
+    for (uint32_t e = b * blockDim.x + threadIdx.x; e < total; e += BRICK_BLOCKS * blockDim.x) {
         const uint32_t brick = e >> 6, r = brick / nbx;
         const uint32_t ix = (brick - r * nbx) * 8u + (e & 7u);
         const uint32_t iz = r / nby;
@@ -122,32 +127,28 @@ __global__ void __launch_bounds__(256) k_brick(const JobDev *__restrict__ jobs, 
     }
 }
 
-__global__ void k_put_jobs(JobDev *dst, JobPack pack) {
-    const int words = (int)(sizeof(JobDev) / sizeof(uint64_t)) * pack.count;
+// What a call needs before its first pass, in one launch (a launch costs some 5 us, more than
+// any of this on a small batch: with the table, the orders, the status word and the bricks
+// in a launch each and the offsets scanned, 10 launches and 120 us for 92,160 straight rows at
+// 200 x 200; 110 now with 5).
+// Block 0: the pack's jobs and orders to the workspace, the header's words reset (a kernel, so
+// that a captured graph holds no memset node).  The other blocks, BRICK_BLOCKS for each job:
+// its bricks.
+__global__ void __launch_bounds__(256) k_put_jobs(JobDev *dst, int32_t *order, WsHeader *h, JobPack pack) {
+    if (blockIdx.x > 0) {
+        fill_bricks(pack.jobs[(blockIdx.x - 1) / BRICK_BLOCKS], (blockIdx.x - 1) % BRICK_BLOCKS);
+        return;
+    }
+    const int words = (int)(sizeof(JobDev) / sizeof(uint64_t)) * pack.count, t = (int)threadIdx.x;
     const uint64_t *src = reinterpret_cast<const uint64_t *>(pack.jobs);
     uint64_t *out = reinterpret_cast<uint64_t *>(dst + pack.first);
-    for (int w = threadIdx.x; w < words; w += blockDim.x) out[w] = src[w];
-}
-
-constexpr int ORDER_PER_PACK = 900;
-struct OrderPack {
-    int32_t count;
-    int32_t first;
-    int32_t idx[ORDER_PER_PACK];
-};
-
-__global__ void k_put_order(int32_t *dst, OrderPack pack) {
-    for (int i = threadIdx.x; i < pack.count; i += blockDim.x) dst[pack.first + i] = pack.idx[i];
-}
-
-__global__ void k_clear_status(WsHeader *h) {
-    if (threadIdx.x == 0) h->status = PCT_OK;
-}
-
-// The tile counters of the persistent emit, reset by the call that uses them (a kernel,
-// so that a captured graph holds no memset node).
-__global__ void k_reset_queue(WsHeader *h) {
-    if (threadIdx.x < 2) h->qnext[threadIdx.x] = 0ull;
+    for (int w = t; w < words; w += blockDim.x) out[w] = src[w];
+    if (t < pack.count) {
+        order[pack.first + t] = pack.order[0][t];
+        order[pack.n_jobs + pack.first + t] = pack.order[1][t];
+    }
+    if (t == 0 && (pack.clear & CLEAR_STATUS)) h->status = PCT_OK;
+    if (t < 2 && (pack.clear & CLEAR_QUEUE)) h->qnext[t] = 0ull;
 }
 
 __device__ __forceinline__ void set_status(int32_t *status, int32_t code) { set_status_dev(status, code); }
@@ -305,9 +306,17 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_tiles(const JobDev *__res
 }
 
 // row_ptr[r] = (offset of the tile within its job) + exclusive scan of the tile's counts.
+// SUMS: the offset is summed here, from the sums of the job's earlier tiles, and the job totals
+// are written here too, so that k_scan_tiles (one block, and a launch) is not needed.  A job of
+// n tiles reads n^2 / 2 sums then; up to SUM_READS of n^2 in all (one job of 4,096 tiles), where
+// that is still the shorter way (2,500 tiles: 7.0 us, scan and offsets 10.3 and a launch; 3,907:
+// 11.3 and 13.8; 11,520: 48.6 and 32.5).
+constexpr int64_t SUM_READS = int64_t(1) << 24;
+template <bool SUMS>
 __global__ void __launch_bounds__(TILE) k_row_ptr(const JobDev *__restrict__ jobs, const int32_t *__restrict__ corder,
                                                   int n_jobs, const int32_t *__restrict__ counts,
-                                                  const int64_t *__restrict__ offs) {
+                                                  const int64_t *__restrict__ sums, const int64_t *__restrict__ offs,
+                                                  int64_t *__restrict__ nnz_total) {
     __shared__ int64_t sc[TILE];
     __shared__ int wsum[TILE / WAVE];
     const int64_t tile = blockIdx.x;
@@ -315,8 +324,26 @@ __global__ void __launch_bounds__(TILE) k_row_ptr(const JobDev *__restrict__ job
     const JobDev &J = jobs[jid];
     const int64_t r = (tile - J.tile_base) * TILE + threadIdx.x;
     const int64_t c = (r < J.row_count) ? counts[J.count_off + r] : 0;
-    const int64_t base = offs[tile] - offs[J.tile_base];
-    if (offs[tile + 1] - offs[tile] <= INT32_MAX) {
+    int64_t base, own;
+    if constexpr (SUMS) {
+        __shared__ int64_t part[TILE / WAVE];
+        own = sums[tile];
+        int64_t v = 0;
+        for (int64_t k = J.tile_base + threadIdx.x; k < tile; k += TILE) v += sums[k];
+        for (int off = WAVE / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
+        if (threadIdx.x % WAVE == 0) part[threadIdx.x / WAVE] = v;
+        __syncthreads();
+        base = 0;
+        for (int i = 0; i < TILE / WAVE; ++i) base += part[i];
+        if (threadIdx.x == 0 && tile == J.tile_base + J.n_tiles - 1) nnz_total[jid] = J.row_ptr[J.row_count] = base + own;
+        if (blockIdx.x == 0)   // the jobs that have no tile
+            for (int j = threadIdx.x; j < n_jobs; j += TILE)
+                if (jobs[j].n_tiles == 0) nnz_total[j] = jobs[j].row_ptr[0] = 0;
+    } else {
+        base = offs[tile] - offs[J.tile_base];
+        own = offs[tile + 1] - offs[tile];
+    }
+    if (own <= INT32_MAX) {
         // the tile's entries fit in 32 bits: scans per wave (DPP) and over the 4 waves
         const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
         const int incl = wave_incl_scan((int)c);
@@ -1160,15 +1187,15 @@ struct Prepared {
     int64_t dim_base[2] = {0, 0}, dim_tiles[2] = {0, 0};   // emit tiles of the 2D jobs, then the 3D jobs
     int64_t cdim_base[2] = {0, 0}, cdim_tiles[2] = {0, 0}; // count tiles likewise
     bool lane_rows[2] = {false, false};                      // 2D, 3D: rows of the per-lane walk are possible
-    bool any_bricks = false;                                 // some job has a bricked copy of x to fill
     explicit Prepared(int32_t n) : H(n) {}
 };
 
-// Job table (caller's order; the count pass uses it as is) and the emit launch order,
-// both uploaded through kernel arguments.  bricks: jobs that allow it get a bricked
-// copy of x in the workspace (every call on a workspace sized by pct_workspace_bytes).
+// Job table (caller's order; the count pass uses it as is) and the launch orders, uploaded
+// through kernel arguments; the header words in `clear` reset.  bricks: jobs that allow it
+// have a bricked copy of x in the workspace (every call on a workspace sized by
+// pct_workspace_bytes), filled here if `fill`.
 static pct_status prepare(int32_t n_jobs, const pct_job *jobs, void *ws, size_t ws_bytes, Prepared &P,
-                          hipStream_t st, bool bricks = true) {
+                          hipStream_t st, uint32_t clear, bool fill, bool bricks = true) {
     int64_t *rc = P.H.rc;
     JobDev *jd = P.H.jobs;
     size_t *bb = P.H.bb;
@@ -1187,7 +1214,6 @@ static pct_status prepare(int32_t n_jobs, const pct_job *jobs, void *ws, size_t 
             jd[j].xb = reinterpret_cast<float *>((char *)ws + boff);
             jd[j].nbx = (jd[j].n[0] + 7) / 8;
             jd[j].nby = (jd[j].n[1] + 7) / 8;
-            P.any_bricks = true;
         }
         boff += align256(bb[j]);
     }
@@ -1253,23 +1279,24 @@ static pct_status prepare(int32_t n_jobs, const pct_job *jobs, void *ws, size_t 
     P.total_etiles = etile;
     char *w = (char *)ws;
     JobDev *dst = reinterpret_cast<JobDev *>(w + P.L.jobs_off);
-    for (int first = 0; first < n_jobs; first += JOBS_PER_PACK) {
+    int32_t *odst = reinterpret_cast<int32_t *>(w + P.L.order_off);
+    fill = fill && P.L.total_tiles > 0;
+    for (int first = 0; first == 0 || first < n_jobs; first += JOBS_PER_PACK) {
         JobPack pack;
         memset(&pack, 0, sizeof pack);
         pack.first = first;
         pack.count = (n_jobs - first < JOBS_PER_PACK) ? n_jobs - first : JOBS_PER_PACK;
-        for (int k = 0; k < pack.count; ++k) pack.jobs[k] = jd[first + k];
-        hipLaunchKernelGGL(k_put_jobs, dim3(1), dim3(256), 0, st, dst, pack);
-    }
-    // the emit order, then the count order
-    int32_t *odst = reinterpret_cast<int32_t *>(w + P.L.order_off);
-    for (int first = 0; first < 2 * n_jobs; first += ORDER_PER_PACK) {
-        OrderPack pack;
-        memset(&pack, 0, sizeof pack);
-        pack.first = first;
-        pack.count = (2 * n_jobs - first < ORDER_PER_PACK) ? 2 * n_jobs - first : ORDER_PER_PACK;
-        for (int k = 0; k < pack.count; ++k) pack.idx[k] = order[first + k];
-        hipLaunchKernelGGL(k_put_order, dim3(1), dim3(256), 0, st, odst, pack);
+        pack.n_jobs = n_jobs;
+        pack.clear = first == 0 ? clear : 0;
+        bool any = false;
+        for (int k = 0; k < pack.count; ++k) {
+            pack.jobs[k] = jd[first + k];
+            pack.order[0][k] = order[first + k];
+            pack.order[1][k] = corder[first + k];
+            any = any || jd[first + k].xb;
+        }
+        const unsigned blocks = 1u + (fill && any ? (unsigned)pack.count * BRICK_BLOCKS : 0u);
+        hipLaunchKernelGGL(k_put_jobs, dim3(blocks), dim3(256), 0, st, dst, odst, (WsHeader *)w, pack);
     }
     return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
 }
@@ -1300,7 +1327,6 @@ static void launch_emit(const Prepared &P, bool has2, bool has3, hipStream_t s, 
     const dim3 block(TILE);
     const int64_t n2 = has2 ? P.dim_tiles[0] : 0, n3 = has3 ? P.dim_tiles[1] : 0;
     if (P.cfg.blocks_per_cu > 0) {
-        hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(64), 0, s, hdr);
         const int64_t cap = (int64_t)cu_count() * P.cfg.blocks_per_cu;
         if (n2 > 0)
             hipLaunchKernelGGL((k_emit_queue<R, STORE, 2>), dim3((unsigned)(n2 < cap ? n2 : cap)), block, 0, s, J,
@@ -1419,11 +1445,10 @@ static pct_status count_common(int32_t n_jobs, const pct_job *jobs, void *ws, si
     hipStream_t s = (hipStream_t)stream;
     if (!ws) return PCT_EWORKSPACE;
     Prepared P(n_jobs);
-    st = prepare(n_jobs, jobs, ws, ws_bytes, P, s);
+    st = prepare(n_jobs, jobs, ws, ws_bytes, P, s, clear_status ? CLEAR_STATUS : 0u, false);
     if (st != PCT_OK) return st;
     char *w = (char *)ws;
-    if (clear_status) hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, s, (WsHeader *)w);
-    if (n_jobs == 0) return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
+    if (n_jobs == 0) return PCT_OK;
     const JobDev *J = (const JobDev *)(w + P.L.jobs_off);
     const int32_t *corder = (const int32_t *)(w + P.L.order_off) + n_jobs;
     int64_t *sums = (int64_t *)(w + P.L.sums_off);
@@ -1438,8 +1463,17 @@ static pct_status count_common(int32_t n_jobs, const pct_job *jobs, void *ws, si
             launch_count<float, true>(P.cdim_base, P.cdim_tiles, s, J, corder, n_jobs, counts, sums,
                                       (int32_t *)(w + P.L.flags_off), w + P.L.rows_off);
     }
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(SCAN_THREADS), 0, s, J, n_jobs, T, sums, offs, nnz_total_dev);
-    if (T > 0) hipLaunchKernelGGL(k_row_ptr, dim3((unsigned)T), dim3(TILE), 0, s, J, corder, n_jobs, counts, offs);
+    int64_t reads = 0;
+    for (int32_t j = 0; j < n_jobs && reads <= SUM_READS; ++j) reads += std::min(P.H.jobs[j].n_tiles, SUM_READS) * P.H.jobs[j].n_tiles;
+    if (T > 0 && reads <= SUM_READS) {
+        hipLaunchKernelGGL((k_row_ptr<true>), dim3((unsigned)T), dim3(TILE), 0, s, J, corder, n_jobs, counts, sums,
+                           (const int64_t *)nullptr, nnz_total_dev);
+    } else {
+        hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(SCAN_THREADS), 0, s, J, n_jobs, T, sums, offs, nnz_total_dev);
+        if (T > 0)
+            hipLaunchKernelGGL((k_row_ptr<false>), dim3((unsigned)T), dim3(TILE), 0, s, J, corder, n_jobs, counts,
+                               (const int64_t *)nullptr, offs, (int64_t *)nullptr);
+    }
     return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
 }
 
@@ -1453,18 +1487,12 @@ static pct_status emit_common(int32_t n_jobs, const pct_job *jobs, void *ws, siz
     hipStream_t s = (hipStream_t)stream;
     if (!ws) return PCT_EWORKSPACE;
     Prepared P(n_jobs);
-    st = prepare(n_jobs, jobs, ws, ws_bytes, P, s, bricks);
+    // WEPL only runs its own count pass: the status word starts afresh, as in a count call
+    st = prepare(n_jobs, jobs, ws, ws_bytes, P, s, CLEAR_QUEUE | (store ? 0u : CLEAR_STATUS), true, bricks);
     if (st != PCT_OK) return st;
     char *w = (char *)ws;
     const JobDev *J = (const JobDev *)(w + P.L.jobs_off);
-    if (P.any_bricks && P.L.total_tiles > 0)
-        for (int32_t j0 = 0; j0 < n_jobs; j0 += 65535) {
-            const int32_t nj = n_jobs - j0 < 65535 ? n_jobs - j0 : 65535;
-            hipLaunchKernelGGL(k_brick, dim3(BRICK_BLOCKS, (unsigned)nj), dim3(256), 0, s, J, j0);
-        }
     int32_t *status = &((WsHeader *)w)->status;
-    // WEPL only runs its own count pass: the status word starts afresh, as in a count call
-    if (!store) hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, s, (WsHeader *)w);
     const int64_t T = P.L.total_tiles;
     if (T == 0) return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
     const bool mixed = jobs[0].precision == PCT_MIXED;
