@@ -111,19 +111,41 @@ struct JobPack {
 // [8 by, 8 by + 8) of plane z, x fastest; the bricks follow x, then y, then z, so that a
 // 128-byte line covers an 8 x 4 patch of a plane.  Voxels past the grid are 0; no gather
 // index reaches them.  The copy has fewer than 2^31 elements (brick_elems).
+//
+// Four voxels of a brick row per thread (x holds them side by side), four such in flight: with
+// one voxel at a time the bricks of 200 x 200 x 160 voxels (51 MB in and out) took 37 us, for
+// latency; 12.8 so (4.0 TB/s), and 256 x 256 x 160 voxels 67 and 26 us.
 constexpr int BRICK_BLOCKS = 512;
 __device__ __forceinline__ void fill_bricks(const JobDev &J, uint32_t b) {
     float *xb = J.xb;
     if (!xb) return;
     const uint32_t nbx = (uint32_t)J.nbx, nby = (uint32_t)J.nby, n0 = (uint32_t)J.n[0], n1 = (uint32_t)J.n[1];
-    const uint32_t total = nbx * nby * (uint32_t)J.n[2] * 64u;
+    const uint32_t quads = nbx * nby * (uint32_t)J.n[2] * 16u, step = BRICK_BLOCKS * blockDim.x;
     const float *x = J.x;
-    for (uint32_t e = b * blockDim.x + threadIdx.x; e < total; e += BRICK_BLOCKS * blockDim.x) {
-        const uint32_t brick = e >> 6, r = brick / nbx;
-        const uint32_t ix = (brick - r * nbx) * 8u + (e & 7u);
-        const uint32_t iz = r / nby;
-        const uint32_t iy = (r - iz * nby) * 8u + ((e >> 3) & 7u);
-        xb[e] = (ix < n0 && iy < n1) ? x[(size_t)ix + (size_t)n0 * ((size_t)iy + (size_t)n1 * iz)] : 0.0f;
+    constexpr int U = 4;
+    for (uint32_t q0 = b * blockDim.x + threadIdx.x; q0 < quads; q0 += U * step) {   // quads < 2^29
+        float4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t q = q0 + (uint32_t)u * step, brick = q >> 4, r = brick / nbx;
+            const uint32_t ix = (brick - r * nbx) * 8u + (q & 1u) * 4u;
+            const uint32_t iz = r / nby;
+            const uint32_t iy = (r - iz * nby) * 8u + ((q >> 1) & 7u);
+            v[u] = float4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (q < quads && iy < n1) {
+                const float *p = x + (size_t)ix + (size_t)n0 * ((size_t)iy + (size_t)n1 * iz);
+                if (ix + 3u < n0) {
+                    __builtin_memcpy(&v[u], p, sizeof v[u]);   // (as aligned as a float)
+                } else {
+                    if (ix < n0) v[u].x = p[0];
+                    if (ix + 1u < n0) v[u].y = p[1];
+                    if (ix + 2u < n0) v[u].z = p[2];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (q0 + (uint32_t)u * step < quads) reinterpret_cast<float4 *>(xb)[q0 + (uint32_t)u * step] = v[u];
     }
 }
 
