@@ -45,36 +45,42 @@ constexpr int WAVE = 64;
 // of the ray are the same line at the parameters tS (in [0, 1]) and tE (in [M-1, M]):
 // item end m is F(min(max(m, tS), tE)).  On the dominant axis F(tS) is the clipped start
 // point exactly; elsewhere the ends agree with the clipped points to rounding.
-template <typename R>
-struct RayP {
-    R c0[3], c1[3];
-    R tS, tE;
-    int32_t M;              // items; 0 when the ray misses the box
-    int32_t lo[3], hi[3];   // voxel index range between the end voxels, per axis
+// c: per axis c0, c1; t: tS, tE; lohi: per axis the voxel index range between the end voxels.
+template <typename R, int DIM>
+struct alignas(2 * sizeof(R)) RayP {
+    R c[DIM][2], t[2];
+    int32_t lohi[DIM][2];
 };
 
 // The spline between entry and exit: N items, one per chord.  Sample m (0 <= m <= N) is
 // F(m) = ((c3 m + c2) m + c1) m + c0: c0 is the entry point, F(N) the exit point to
-// rounding.  win: per axis up to two sample ranges [a, b] (a < b; unused: -1, -1)
-// outside of which the computed samples are strictly monotone in that coordinate.
-template <typename R>
-struct SplP {
-    R c0[3], c1[3], c2[3], c3[3];
-    int32_t N;
-    int32_t win[3][4];
+// rounding (c: per axis c0, c1, then c2, c3).  win: per axis up to two sample ranges [a, b]
+// (a < b; unused: -1, -1) outside of which the computed samples are strictly monotone in
+// that coordinate.
+template <typename R, int DIM>
+struct alignas(16) SplP {
+    int32_t win[DIM][4];
+    R c[DIM][2][2];
 };
 
-// Per-row path description, written by the count pass into the workspace.
-template <typename R>
-struct RowV {
+// Per-row path description, written by the count pass into the workspace: the fields that are
+// known together make 16 bytes (FP64), which one store writes.  Only the grid's axes are held.
+// A 2D row takes 256 bytes, a 3D row 368, the part that a straight row reads 96 and 128.
+// Stored field by field, with three axes and 368 bytes in 2D too, the count pass of 2,949,120
+// curved 2D rows took 435 us (359 so), the whole call 5.81 ms (5.64); 640,000 straight 2D rows
+// 525 us (517).
+template <typename R, int DIM>
+struct alignas(16) RowV {
     int32_t kind;           // 0: no entry, 1: one ray, 2: ray + spline + ray, 3: per-lane walk
     int32_t fast;           // every item crosses each axis at most once
     double bfac;            // WEPL noise factor 1 + r z
-    RayP<R> ray[2];         // ray[0]: the straight path, or the ray into the entry point
-    SplP<R> spl;
+    int32_t M[4];           // items of ray[0] and ray[1] (0 when it misses the box), of the spline
+    RayP<R, DIM> ray[2];    // ray[0]: the straight path, or the ray into the entry point
+    SplP<R, DIM> spl;
 };
 
-// Storage of the descriptions.  Each job has RV_TILE * rv_bytes bytes per count tile.
+// Storage of the descriptions.  Each job has RV_TILE * rv_bytes bytes per count tile (what a 3D
+// row takes).
 // Inside it, rows are grouped by 2^S: 16-byte chunk c of row i of a group sits at byte
 // (c * 2^S + i) * 16 of the group's block.  S = 8, for 2D and 3D grids alike:
 // chunk-transposed over a whole tile, so that the count pass (one lane per row) writes
@@ -85,7 +91,7 @@ struct RowV {
 // A field never straddles a chunk (all are 4 or 8 bytes at their natural alignment).
 constexpr int RV_TILE = 256;
 template <typename R>
-constexpr size_t rv_bytes() { return (sizeof(RowV<R>) + 15) & ~size_t(15); }
+constexpr size_t rv_bytes() { return sizeof(RowV<R, 3>); }
 template <int DIM>
 constexpr int rv_shift() { return 8; }
 
@@ -120,8 +126,15 @@ __device__ __forceinline__ RowRefD<R, DIM> row_ref(char *rowbuf, const JobDev &J
 }
 
 #define RV(w, member) \
-    (w).template at<typename std::remove_reference<decltype(((RowV<R> *)nullptr)->member)>::type>( \
-        __builtin_offsetof(RowV<R>, member))
+    (w).template at<typename std::remove_reference<decltype(((RowV<R, DIM> *)nullptr)->member)>::type>( \
+        __builtin_offsetof(RowV<R, DIM>, member))
+// Two neighbouring fields of type R, or four of int32_t, in one store.
+#define RV_PUT2(w, member, a, b) \
+    (w).template at<typename PairOf<R>::T>(__builtin_offsetof(RowV<R, DIM>, member)) = typename PairOf<R>::T{a, b}
+#define RV_PUT4(w, member, a, b, c, d) \
+    (w).template at<int4>(__builtin_offsetof(RowV<R, DIM>, member)) = int4{a, b, c, d}
+template <typename R> struct PairOf { using T = double2; };
+template <> struct PairOf<float> { using T = float2; };
 
 // Lane i's value of v, as a wave-uniform value.
 __device__ __forceinline__ int64_t readlane_i64(int64_t v, int i) {
@@ -142,8 +155,8 @@ __device__ __forceinline__ double uniform_f64(const LdsRow &wl, size_t off) {
     const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)v.y);
     return __builtin_bit_cast(double, lo | (hi << 32));
 }
-#define RL_I32(wl, member) uniform_i32((wl), __builtin_offsetof(RowV<R>, member))
-#define RL_F64(wl, member) uniform_f64((wl), __builtin_offsetof(RowV<R>, member))
+#define RL_I32(wl, member) uniform_i32((wl), __builtin_offsetof(RowV<R, DIM>, member))
+#define RL_F64(wl, member) uniform_f64((wl), __builtin_offsetof(RowV<R, DIM>, member))
 
 template <typename R> __device__ __forceinline__ R r_fmax(R a, R b) {
     if constexpr (std::is_same<R, float>::value) return fmaxf(a, b); else return fmax(a, b);
@@ -209,6 +222,7 @@ __device__ __forceinline__ bool make_ray(const JobDev &J, const R A[3], const R 
     // face of item end m: isd + m (upwards) or isd + 1 - m (downwards)
     const R c0d = R(sdom > 0 ? isd : isd + 1), c1d = R(sdom);
     bool one = true;
+    int32_t rlo[DIM], rhi[DIM];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         R c0 = R(0), c1 = R(0);
@@ -226,10 +240,11 @@ __device__ __forceinline__ bool make_ray(const JobDev &J, const R A[3], const R 
                 if (!((rd < R(0) ? -rd : rd) < R(0.999))) one = false;
             }
         }
-        RV(w, ray[WHICH].c0[d]) = c0;
-        RV(w, ray[WHICH].c1[d]) = c1;
-        RV(w, ray[WHICH].lo[d]) = lo_;
-        RV(w, ray[WHICH].hi[d]) = hi_;
+        if (d < DIM) {
+            RV_PUT2(w, ray[WHICH].c[d], c0, c1);
+            rlo[d] = lo_;
+            rhi[d] = hi_;
+        }
         // the piece as the emit reads it back (lane_ray: the range kept inside the grid)
         const int top = J.n[d] - 1;
         const int clo = lo_ < 0 ? 0 : (lo_ > top ? top : lo_);
@@ -243,9 +258,14 @@ __device__ __forceinline__ bool make_ray(const JobDev &J, const R A[3], const R 
     const int32_t M = hit ? abs(ied - isd) + 1 : 0;
     // end parameters on the dominant axis (c1 = +-1): F(t) = c0 + c1 t
     const R tS = hit ? (fsd - c0d) * c1d : R(0), tE = hit ? (fed - c0d) * c1d : R(0);
-    RV(w, ray[WHICH].M) = M;
-    RV(w, ray[WHICH].tS) = tS;
-    RV(w, ray[WHICH].tE) = tE;
+    RV_PUT2(w, ray[WHICH].t, tS, tE);
+    // (16 bytes at once where they lie in one chunk: FP64)
+#pragma unroll
+    for (int d = 0; d + 1 < DIM && sizeof(R) == 8; d += 2)
+        RV_PUT4(w, ray[WHICH].lohi[d], rlo[d], rhi[d], rlo[d + 1], rhi[d + 1]);
+#pragma unroll
+    for (int d = sizeof(R) == 8 ? DIM / 2 * 2 : 0; d < DIM; ++d)
+        w.template at<int2>(__builtin_offsetof(RowV<R, DIM>, ray[WHICH].lohi[d])) = int2{rlo[d], rhi[d]};
     lp.M = M;
     lp.tS = tS;
     lp.tE = tE;
@@ -364,34 +384,35 @@ template <typename R, int DIM, int WHICH, class W>
 __device__ __forceinline__ void lane_ray(const JobDev &J, W w, LaneP<R> &p) {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        p.c0[d] = RV(w, ray[WHICH].c0[d]);
-        p.c1[d] = RV(w, ray[WHICH].c1[d]);
-        p.c2[d] = R(0);
-        p.c3[d] = R(0);
+        p.c0[d] = p.c1[d] = p.c2[d] = p.c3[d] = R(0);
+        p.lo[d] = p.hi[d] = 0;
+        if (d >= DIM) continue;
+        p.c0[d] = RV(w, ray[WHICH].c[d][0]);
+        p.c1[d] = RV(w, ray[WHICH].c[d][1]);
         const int top = J.n[d] - 1;
-        const int rlo = RV(w, ray[WHICH].lo[d]), rhi = RV(w, ray[WHICH].hi[d]);
+        const int rlo = RV(w, ray[WHICH].lohi[d][0]), rhi = RV(w, ray[WHICH].lohi[d][1]);
         const int lo = rlo < 0 ? 0 : (rlo > top ? top : rlo);
         const int hi = rhi < lo ? lo : (rhi > top ? top : rhi);
         p.lo[d] = lo;
         p.hi[d] = hi;
     }
-    p.tS = RV(w, ray[WHICH].tS);
-    p.tE = RV(w, ray[WHICH].tE);
-    p.M = RV(w, ray[WHICH].M);
+    p.tS = RV(w, ray[WHICH].t[0]);
+    p.tE = RV(w, ray[WHICH].t[1]);
+    p.M = RV(w, M[WHICH]);
 }
 
 template <typename R, int DIM, class W>
 __device__ __forceinline__ void lane_spline(const JobDev &J, W w, LaneP<R> &p) {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        p.c0[d] = RV(w, spl.c0[d]);
-        p.c1[d] = RV(w, spl.c1[d]);
-        p.c2[d] = RV(w, spl.c2[d]);
-        p.c3[d] = RV(w, spl.c3[d]);
+        p.c0[d] = d < DIM ? RV(w, spl.c[d < DIM ? d : 0][0][0]) : R(0);
+        p.c1[d] = d < DIM ? RV(w, spl.c[d < DIM ? d : 0][0][1]) : R(0);
+        p.c2[d] = d < DIM ? RV(w, spl.c[d < DIM ? d : 0][1][0]) : R(0);
+        p.c3[d] = d < DIM ? RV(w, spl.c[d < DIM ? d : 0][1][1]) : R(0);
         p.lo[d] = 0;
         p.hi[d] = J.n[d] - 1;
     }
-    p.M = RV(w, spl.N);
+    p.M = RV(w, M[2]);
     p.tS = R(0);
     p.tE = R(p.M);
 }
@@ -955,9 +976,9 @@ __device__ __forceinline__ void wave_row(const JobDev &J, LdsRow wl, int kind, R
     // item counts as the count pass writes them; the bounds only matter for a
     // description it did not write (the walk then stays finite and the count check fails)
     const int mmax = J.nmax + 1;
-    const int M0 = min(max(RL_I32(wl, ray[0].M), 0), mmax);
-    const int Ns = (!RAY && kind == 2) ? min(max(RL_I32(wl, spl.N), 0), (1 << 22) + 1) : 0;
-    const int M1 = (!RAY && kind == 2) ? min(max(RL_I32(wl, ray[1].M), 0), mmax) : 0;
+    const int M0 = min(max(RL_I32(wl, M[0]), 0), mmax);
+    const int Ns = (!RAY && kind == 2) ? min(max(RL_I32(wl, M[2]), 0), (1 << 22) + 1) : 0;
+    const int M1 = (!RAY && kind == 2) ? min(max(RL_I32(wl, M[1]), 0), mmax) : 0;
     const int T = M0 + Ns + M1;
     n_entries = 0;
     if (T == 0) return;
@@ -1155,7 +1176,7 @@ template <int DIM, typename TW>
 __device__ __forceinline__ void wave_ray_row(const JobDev &J, RowRefD<double, DIM> w, LdsRow wl, RowOut<TW> &out,
                                              int lane, int64_t &n_entries) {
     using R = double;
-    const int M = min(max(RL_I32(wl, ray[0].M), 0), J.nmax + 1);
+    const int M = min(max(RL_I32(wl, M[0]), 0), J.nmax + 1);
     n_entries = 0;
     if (M == 0) return;
     const int K = (M + WAVE - 1) / WAVE;
@@ -1296,14 +1317,14 @@ __device__ __forceinline__ RowSetup setup_row(const JobDev &J, int64_t g, RowRef
     int kind = 0, fast = (DIM == 3 ? (int64_t)J.n[0] * J.n[1] : (int64_t)J.n[0]) < (1 << 23) ? 1 : 0;
     int64_t cross = 0;        // face crossings of the pieces
     bool any = false;         // a piece with items
-    RV(w, spl.N) = 0;
-    RV(w, ray[1].M) = 0;
+    int32_t M0 = 0, M1 = 0, Ns = 0;
     if (!p.curved) {
         R lo = ninf, hi = pinf;
         const bool hit = clip_box<R, DIM>(J, p.Q, p.u, lo, hi);
         kind = hit ? 1 : 0;
         LaneP<R> lp;
         if (!make_ray<R, DIM, 0>(J, p.Q, p.u, lo, hi, hit, w, lp)) fast = 0;
+        M0 = lp.M;
         if (lp.M > 0) {
             cross += ray_piece_crossings<R, DIM>(lp);
             any = true;
@@ -1319,17 +1340,18 @@ __device__ __forceinline__ RowSetup setup_row(const JobDev &J, int64_t g, RowRef
         const bool in = hull_inside<R, DIM>(J, p.P0) && hull_inside<R, DIM>(J, p.P1) &&
                         hull_inside<R, DIM>(J, b1) && hull_inside<R, DIM>(J, b2);
         kind = in ? 2 : 3;
-        RV(w, ray[0].M) = 0;
         if (in) {
             R lo = ninf, hi = R(0);
             bool hit = clip_box<R, DIM>(J, p.P0, p.d0, lo, hi);
             LaneP<R> lp;
             if (!make_ray<R, DIM, 0>(J, p.P0, p.d0, lo, hi, hit, w, lp)) fast = 0;
+            M0 = lp.M;
             if (lp.M > 0) cross += ray_piece_crossings<R, DIM>(lp);
             lo = R(0);
             hi = pinf;
             hit = clip_box<R, DIM>(J, p.P1, p.d1, lo, hi);
             if (!make_ray<R, DIM, 1>(J, p.P1, p.d1, lo, hi, hit, w, lp)) fast = 0;
+            M1 = lp.M;
             if (lp.M > 0) cross += ray_piece_crossings<R, DIM>(lp);
             any = true;   // the spline has N >= 1 items
             // the spline as the emit reads it back (lane_spline): t in [0, N], the grid's range
@@ -1344,12 +1366,10 @@ __device__ __forceinline__ RowSetup setup_row(const JobDev &J, int64_t g, RowRef
                 const R ih = (d < DIM) ? R(J.invh[d]) : R(0);
                 const R fS = (d < DIM) ? (p.P0[d] - R(J.o[d])) * ih : R(0);
                 const R c1 = p.c1[d] * ih * iN, c2 = p.c2[d] * ih * iN2, c3 = p.c3[d] * ih * iN3;
-                RV(w, spl.c0[d]) = fS;
-                RV(w, spl.c1[d]) = c1;
-                RV(w, spl.c2[d]) = c2;
-                RV(w, spl.c3[d]) = c3;
                 int32_t win[4] = {-1, -1, -1, -1};
                 if (d < DIM) {
+                    RV_PUT2(w, spl.c[d][0], fS, c1);
+                    RV_PUT2(w, spl.c[d][1], c2, c3);
                     spline_windows<R>(c1, c2, c3, p.N, thr, win);
                     // a chord moves less than one voxel along d when |F'| < 1 over [0, N]
                     if (!(spline_max_rate<R>(c1, c2, c3, p.N) < R(0.999))) fast = 0;
@@ -1360,13 +1380,13 @@ __device__ __forceinline__ RowSetup setup_row(const JobDev &J, int64_t g, RowRef
                     sp.lo[d] = 0;
                     sp.hi[d] = J.n[d] - 1;
                     cross += spline_axis_crossings<R>(sp, d, win);
+                    RV_PUT4(w, spl.win[d], win[0], win[1], win[2], win[3]);
                 }
-#pragma unroll
-                for (int k = 0; k < 4; ++k) RV(w, spl.win[d][k]) = win[k];
             }
-            RV(w, spl.N) = p.N;
+            Ns = p.N;
         }
     }
+    RV_PUT4(w, M, M0, M1, Ns, 0);
     RV(w, kind) = kind;
     RV(w, fast) = fast;
     double bfac = 1.0;
@@ -1411,11 +1431,14 @@ template <typename R, int DIM, bool STORE>
 __device__ __forceinline__ void emit_rows_wave(const JobDev &J, char *rowbuf, int64_t r0, int nr, int lane,
                                                uint2 *stage, int32_t *status) {
     using TW = typename std::conditional<std::is_same<R, double>::value, double, float>::type;
-    constexpr int NC = (int)(rv_bytes<R>() / 16);
-    static_assert(NC <= WAVE && 2 * NC <= STAGE_DESC, "a description is copied with one chunk per lane");
+    static_assert(sizeof(RowV<R, DIM>) / 16 <= WAVE && sizeof(RowV<R, DIM>) / 8 <= STAGE_DESC,
+                  "a description is copied with one chunk per lane");
+    // the chunks of a row that its walk reads (a straight job: no second ray, no spline)
+    const int nc = J.path == PCT_STRAIGHT ? (int)((__builtin_offsetof(RowV<R, DIM>, ray[1]) + 15) / 16)
+                                          : (int)(sizeof(RowV<R, DIM>) / 16);
     uint4 *dbuf = reinterpret_cast<uint4 *>(stage + STAGE_ROW_MAX);
     const int64_t rend = (r0 + nr < J.row_count) ? r0 + nr : J.row_count;
-    if (r0 < rend && lane < NC) dbuf[lane] = row_ref<R, DIM>(rowbuf, J, r0).template at<uint4>((size_t)lane * 16);
+    if (r0 < rend && lane < nc) dbuf[lane] = row_ref<R, DIM>(rowbuf, J, r0).template at<uint4>((size_t)lane * 16);
     __builtin_amdgcn_wave_barrier();
     const LdsRow wl{(char *)dbuf};
     // the rows' CSR bounds, read once per wave (lane l: row_ptr[r0 + l] and the next), so
@@ -1432,9 +1455,9 @@ __device__ __forceinline__ void emit_rows_wave(const JobDev &J, char *rowbuf, in
     for (int64_t r = r0; r < rend; ++r) {
         RowOut<TW> out;
         out.dbuf = dbuf;
-        out.dnc = NC;
+        out.dnc = nc;
         out.dnext = make_uint4(0u, 0u, 0u, 0u);
-        if (lane < NC)   // the next row's description (the last row's own at the end of the range)
+        if (lane < nc)   // the next row's description (the last row's own at the end of the range)
             out.dnext = row_ref<R, DIM>(rowbuf, J, r + 1 < rend ? r + 1 : r).template at<uint4>((size_t)lane * 16);
         // (the control fields from the LDS copy, which holds this row's description)
         const int kind = RL_I32(wl, kind);
