@@ -1310,8 +1310,10 @@ struct RowSetup {
 template <typename R, int DIM>
 __device__ __forceinline__ RowSetup setup_row(const JobDev &J, int64_t g, RowRefD<R, DIM> w) {
     PathGeom<R> p;
-    if (J.path == 1) make_path<R, DIM, true>(J, g, p);
-    else make_path<R, DIM, false>(J, g, p);
+    const bool noise = J.noise > 0.0;
+    R zn = R(0);
+    if (J.path == 1) make_path<R, DIM, true>(J, g, p, noise, &zn);
+    else make_path<R, DIM, false>(J, g, p, noise, &zn);
     const R ninf = -r_inf<R>(), pinf = r_inf<R>();
     // fast: every item crosses each axis at most once (and item_fast's column steps hold)
     int kind = 0, fast = (DIM == 3 ? (int64_t)J.n[0] * J.n[1] : (int64_t)J.n[0]) < (1 << 23) ? 1 : 0;
@@ -1389,13 +1391,7 @@ __device__ __forceinline__ RowSetup setup_row(const JobDev &J, int64_t g, RowRef
     RV_PUT4(w, M, M0, M1, Ns, 0);
     RV(w, kind) = kind;
     RV(w, fast) = fast;
-    double bfac = 1.0;
-    if (J.noise > 0.0) {
-        R z1, z2;
-        normal_pair<R>(J.seed, 4, (uint64_t)g, z1, z2);
-        bfac = (double)(R(1) + R(J.noise) * z1);
-    }
-    RV(w, bfac) = bfac;
+    RV(w, bfac) = noise ? (double)(R(1) + R(J.noise) * zn) : 1.0;
     return RowSetup{kind, (kind == 1 || kind == 2) && any ? cross + 1 : 0};
 }
 
