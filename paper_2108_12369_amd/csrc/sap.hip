@@ -1004,8 +1004,16 @@ __global__ void k_sap_uniform(double *w, int32_t M) {
     if (t < M) w[t] = 1.0 / (double)M;
 }
 
-__global__ void k_sap_no_levels(uint8_t *lev, int64_t m) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) lev[i] = 0;
+// Levels of rows one after another, right for any order: strings of one row (level 0), and what
+// a prepare with a caller's order leaves for an iterate without it.
+__global__ void k_sap_one_by_one(SapArgs a, int W) {
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < a.m; p += step) {
+        const int64_t t = ((p + 1) * a.M - 1) / a.m;   // the string of position p
+        const int64_t s0 = t * a.m / a.M, s1 = (t + 1) * a.m / a.M;
+        const int64_t lv = (p - s0) % W, rows = s1 - (p - lv);
+        a.lev[p] = (uint8_t)(lv | ((rows < W ? rows : W) - 1) << 4);
+    }
 }
 
 __global__ void k_sap_clear_status(int32_t *status) {
@@ -1085,13 +1093,17 @@ pct_status launch_levels_w(const SapArgs &a, hipStream_t s) {
     hipLaunchKernelGGL((k_sap_levels<W>), dim3(blocks), dim3(64 * W), bytes, s, a, span);
     return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
 }
+pct_status launch_one_by_one(const SapArgs &a, hipStream_t s) {
+    if (a.m == 0) return PCT_OK;
+    const int64_t blocks = (a.m + 255) / 256;
+    hipLaunchKernelGGL(k_sap_one_by_one, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, s, a,
+                       y_in_lds(a.n) ? SAP_W_LDS : SAP_W_WS);
+    return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
+}
+
 pct_status launch_levels(const SapArgs &a, hipStream_t s) {
     if (a.m == 0 || a.nnz == 0) return PCT_OK;   // no row to project
-    if (longest_string(a) == 1) {                // every batch is one row
-        const int64_t blocks = (a.m + 255) / 256;
-        hipLaunchKernelGGL(k_sap_no_levels, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, s, a.lev, a.m);
-        return hipGetLastError() == hipSuccess ? PCT_OK : PCT_EHIP;
-    }
+    if (longest_string(a) == 1) return launch_one_by_one(a, s);   // every batch is one row
     return y_in_lds(a.n) ? launch_levels_w<SAP_W_LDS>(a, s) : launch_levels_w<SAP_W_WS>(a, s);
 }
 
@@ -1189,7 +1201,8 @@ pct_status pct_sap_prepare(const pct_csr *A, const pct_sap *p, void *ws_dev, siz
     }
     if (!y_in_lds(A->n_cols) && A->nnz > 0) hipLaunchKernelGGL(k_sap_row_length, dim3(1), dim3(LEN_THREADS), 0, s, a);
     if (hipGetLastError() != hipSuccess) return PCT_EHIP;
-    return p->order_dev || together ? PCT_OK : launch_levels(a, s);
+    if (p->order_dev) return launch_one_by_one(a, s);
+    return together ? PCT_OK : launch_levels(a, s);
 }
 
 pct_status pct_sap_iterate(const pct_csr *A, const pct_sap *p, float *x_dev, int32_t n_iter, void *ws_dev,

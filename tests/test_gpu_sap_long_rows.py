@@ -70,3 +70,25 @@ def test_bad_column(P, where, bad):
                                                         np.ones(m * k, np.float32), np.ones(m, np.float32))]
     S = P.Sap(*args, N, n_strings=1, relax=0.8)
     assert S.status() == P.PCT_EINVAL
+
+
+@pytest.mark.parametrize("n", [20000, N])
+@pytest.mark.parametrize("m,M", [(1, 1), (7, 7), (200, 3), (150, 140)])
+def test_prepared_with_an_order_iterated_without(P, oracle, n, m, M):
+    """The coefficients are per row: a prepare with an order serves an iterate in natural order."""
+    rng = np.random.default_rng(m + n)
+    lens = rng.integers(1, 300, m)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    cols = np.concatenate([rng.choice(2000, k, replace=False) for k in lens]).astype(np.int32)
+    vals = rng.uniform(0.05, 2.0, int(rp[-1])).astype(np.float32)
+    b = np.add.reduceat(vals.astype(np.float64) * rng.uniform(0.0, 1.5, n)[cols], rp[:-1]).astype(np.float32)
+    S = P.Sap(*(torch.as_tensor(v, device="cuda") for v in (rp, cols, vals, b)), n, n_strings=M, relax=0.8,
+              order=torch.as_tensor(rng.permutation(m), device="cuda"))
+    S.p.order_dev = None
+    x = torch.zeros(n, device="cuda")
+    S.iterate(x, 2)
+    assert S.status() == 0
+    want = oracle.sap(rp, cols, vals.astype(np.float64), b.astype(np.float64), n, np.zeros(n), n_iter=2, n_strings=M,
+                      relax=0.8)
+    err = float(np.abs(x.cpu().numpy() - want).max())
+    assert err <= 1e-5 * float(np.abs(want).max()) + 1e-6, err
