@@ -173,12 +173,12 @@ def _ptr(t):
 def make_phantom(ph: dict):
     regs = ph["regions"]
     arr = (Region * max(1, len(regs)))()
-    for i, r in enumerate(regs):
-        arr[i].shape = SHAPES[r["shape"]]
-        arr[i].rsp = float(r["rsp"])
-        arr[i].angle_deg = float(r.get("angle_deg", 0.0))
-        arr[i].center[:] = [float(v) for v in list(r["center"]) + [0.0] * (3 - len(r["center"]))]
-        arr[i].semi[:] = [float(v) for v in list(r["semi"]) + [1.0] * (3 - len(r["semi"]))]
+    for reg, r in zip(arr, regs):   # (each element of the array is made anew when it is named)
+        reg.shape = SHAPES[r["shape"]]
+        reg.rsp = float(r["rsp"])
+        reg.angle_deg = float(r.get("angle_deg", 0.0))
+        reg.center[:] = [float(v) for v in list(r["center"]) + [0.0] * (3 - len(r["center"]))]
+        reg.semi[:] = [float(v) for v in list(r["semi"]) + [1.0] * (3 - len(r["semi"]))]
     p = Phantom()
     dim = int(ph["dim"])
     n = list(ph["n"]) + [1] * (3 - len(ph["n"]))
@@ -411,12 +411,17 @@ def simulate(cfg: dict, row_begin: int = 0, row_count: int | None = None, precis
     chord = cfg.get("chord_mm") or 0.0
     if row_count is None:
         row_count = int(bm["n_protons"]) - row_begin
-    if x is None:
-        x = phantom_build(ph, stream=stream, device=device)
+    # one set of descriptors for the phantom, the count and the emit: with a set for each, their
+    # marshalling took 60 us of a small call (1,440 rows at 200 x 200, 5 regions: 141 us, 123 so)
     row_ptr = torch.empty(row_count + 1, dtype=torch.int64, device=device)
     js = JobSet()
     js.add(ph, bm, x, row_ptr=row_ptr, val_dtype=val_dtype, precision=precision,
            row_begin=row_begin, row_count=row_count)
+    job = js.entries[0]
+    if x is None:
+        x = torch.empty(n_voxels(ph), dtype=torch.float32, device=device)
+        _check(lib().pct_phantom_build(job.phantom, _ptr(x), _stream_ptr(stream)), "pct_phantom_build")
+        job.x_dev = _ptr(x)
     ws = torch.empty(max(workspace_bytes(js), 256), dtype=torch.uint8, device=device)
     nnz_t = torch.empty(1, dtype=torch.int64, device=device)
     count_rows(js, ws, nnz_t, stream)
@@ -424,11 +429,12 @@ def simulate(cfg: dict, row_begin: int = 0, row_count: int | None = None, precis
     cols = torch.empty(max(nnz, 1), dtype=torch.int32, device=device)
     vals = torch.empty(max(nnz, 1), dtype=torch.float16 if val_dtype == "f16" else torch.float32, device=device)
     b = torch.empty(max(row_count, 1), dtype=torch.float32, device=device)
-    js2 = JobSet()
-    js2.add(ph, bm, x, row_ptr=row_ptr, cols=cols, vals=vals, b=b, nnz_capacity=nnz,
-            val_dtype=val_dtype, precision=precision, row_begin=row_begin, row_count=row_count,
-            chord_mm=chord)
-    emit_csr(js2, ws, stream)
+    job.cols_dev = _ptr(cols)
+    job.vals_dev = _ptr(vals)
+    job.b_dev = _ptr(b)
+    job.nnz_capacity = nnz
+    job.chord_mm = float(chord)
+    emit_csr(js, ws, stream)
     st = device_status(ws, stream)
     _check(st, "device status after pct_emit_csr")
     return {"x": x, "row_ptr": row_ptr, "cols": cols[:nnz], "vals": vals[:nnz], "b": b[:row_count],
