@@ -322,7 +322,7 @@ typedef struct {
 } pct_sap;
 
 /* Bytes of device workspace for pct_sap_prepare / pct_sap_iterate (0 if a descriptor is
- * invalid): a status word, one coefficient and one byte per row and M x n binary32 string
+ * invalid): a status word, one coefficient and two bytes per row and M x n binary32 string
  * iterates. */
 size_t pct_sap_workspace_bytes(const pct_csr *A, const pct_sap *p);
 
@@ -337,7 +337,8 @@ pct_status pct_sap_prepare(const pct_csr *A, const pct_sap *p, void *ws_dev, siz
  * after pct_sap_prepare on the same A, parameters and workspace.  Each string is one
  * workgroup, which projects rows that share no column side by side (the result is that of
  * the rows one after another, bit for bit).  Its iterate lives in LDS when n binary32 fit a
- * workgroup's LDS, else in the workspace.  The order is read from order_dev by every call.
+ * workgroup's LDS, else in the workspace.  The order is read from order_dev by every call;
+ * calls with and without one may follow one another on one workspace.
  * A row's entries are all applied, also where a column repeats in the row; ||a_i|| is
  * then the norm of their sum per column. */
 pct_status pct_sap_iterate(const pct_csr *A, const pct_sap *p, float *x_dev, int32_t n_iter, void *ws_dev,

@@ -69,7 +69,7 @@ constexpr int SAP_W_LDS = 16, SAP_W_WS = 8;
 constexpr int SAP_NAMES_BITS = 14;   // k_sap_prepare_levels' table: 2^14 words, two blocks per CU
 
 struct SapLayout {
-    size_t coef_off, lev_off, w_off, y_off, total;
+    size_t coef_off, lev_off, olev_off, w_off, y_off, total;
 };
 
 inline size_t a256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -77,8 +77,11 @@ inline size_t a256(size_t v) { return (v + 255) & ~size_t(255); }
 SapLayout sap_layout(int64_t m, int32_t n, int32_t M) {
     SapLayout L;
     L.coef_off = 256;   // [0, 256): status word (same header as the simulator workspace)
-    L.lev_off = L.coef_off + (size_t)m * sizeof(float);   // one byte per position (k_sap_levels)
-    L.w_off = a256(L.lev_off + (size_t)m);
+    // one byte per position (k_sap_levels): the natural order's, written by prepare only, and
+    // those of a caller's order, written by each iterate that is given one
+    L.lev_off = L.coef_off + (size_t)m * sizeof(float);
+    L.olev_off = L.lev_off + (size_t)m;
+    L.w_off = a256(L.olev_off + (size_t)m);
     L.y_off = a256(L.w_off + (size_t)M * sizeof(double));
     L.total = L.y_off + (size_t)M * (size_t)n * sizeof(float);
     return L;
@@ -1215,12 +1218,14 @@ pct_status pct_sap_iterate(const pct_csr *A, const pct_sap *p, float *x_dev, int
     if (p->n_strings > (1 << 30)) return PCT_ERANGE;
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)ws_dev;
-    const SapArgs a = make_args(A, p, ws, L);
+    SapArgs a = make_args(A, p, ws, L);
+    if (p->order_dev) a.lev = (uint8_t *)(ws + L.olev_off);
     float *Y = (float *)(ws + L.y_off);
     const double *w = (const double *)(ws + L.w_off);
     const unsigned avg_blocks = (unsigned)((A->n_cols + 255) / 256);
     // the levels of the natural order are the prepare pass's; those of an order given by
-    // the caller are taken from what its buffer holds now
+    // the caller are taken from what its buffer holds now, and kept apart: calls with and
+    // without an order may follow one another on one workspace
     if (p->order_dev && n_iter > 0) {
         const pct_status ls = launch_levels(a, s);
         if (ls != PCT_OK) return ls;
