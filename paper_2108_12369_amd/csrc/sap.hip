@@ -437,6 +437,11 @@ __global__ __launch_bounds__(64 * W) void k_sap_levels(SapArgs a, uint32_t span)
 // is no faster than the two: 104M entries in 32,000 columns 0.97 and 0.96 ms.
 // The hash table's limit of 1,024 columns per row is not one here: 20,000 rows of 1,283 entries
 // 28.9 -> 0.31 ms (the longer rows had counted as repeating a column).
+// A row of more than MAX_LEN entries is taken to meet every other row of its batch (each of its
+// entries would have to be named), but whether it repeats a column is found: the block sets its
+// columns in the table as a bitmap, 2^19 columns at a time.  Taken as repeating one, it
+// would be projected with atomic adds, and its norm found by store_coef in quadratic time: 2,000
+// rows of 5,000 entries in 100,000 columns 53.7 ms, 0.105 so.
 template <typename VT>
 __global__ __launch_bounds__(64 * SAP_W_WS, 4) void k_sap_prepare_levels(SapArgs a, float relax) {
     constexpr int W = SAP_W_WS, U = 8;         // U: chunks of 64 entries of the row kept in registers
@@ -445,10 +450,11 @@ __global__ __launch_bounds__(64 * SAP_W_WS, 4) void k_sap_prepare_levels(SapArgs
     // a name: 16 high bits for the column (below 2^29), 4 for the row, 12 for the place
     static_assert(W <= 16 && MAX_LEN <= 1 << 12 && LOG_T >= 13, "a name fits a word");
     extern __shared__ uint32_t tab[];
-    __shared__ uint32_t conf[W];
+    __shared__ uint32_t conf[W], longs;   // longs: rows of more than MAX_LEN entries, as bits
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t n = (uint32_t)a.n;
     if (threadIdx.x < W) conf[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) longs = 0u;
     const int64_t longest = (a.m + a.M - 1) / a.M, per = (longest + W - 1) / W, batches = per * a.M;
 
     struct Batch {
@@ -483,11 +489,11 @@ __global__ __launch_bounds__(64 * SAP_W_WS, 4) void k_sap_prepare_levels(SapArgs
     auto process = [&](const Batch &b) {
         bool ok = sound(b);
         const int64_t len = ok ? b.end - b.beg : 0;
-        const bool huge = len > MAX_LEN;                       // taken to meet every row and itself
+        const bool huge = len > MAX_LEN;                       // taken to meet every row
         const int chunks = huge ? 0 : (int)((len + 63) / 64);  // uniform in the wave
         const int32_t *cols = a.cols + (ok ? b.beg : 0);
         uint32_t met = 0u;
-        bool dup = huge;
+        bool dup = false;
         uint64_t todo = 0;   // bit u: chunk u's entry is still to be done (a column outside [0, n) is not)
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -517,12 +523,30 @@ __global__ __launch_bounds__(64 * SAP_W_WS, 4) void k_sap_prepare_levels(SapArgs
             for (int u = U; u < chunks; ++u)
                 if ((todo >> u) & 1) tab[(uint32_t)cols[u * 64 + lane] & (T - 1)] = name(cols[u * 64 + lane], u);
             __syncthreads();
+            if (huge && lane == 0) atomicOr(&longs, 1u << wave);   // (reset before that barrier)
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if ((todo >> u) & 1) check(b.c[u], u);
             for (int u = U; u < chunks; ++u)
                 if ((todo >> u) & 1) check(cols[u * 64 + lane], u);
         } while (__syncthreads_or(todo != 0));   // one entry of every contested word is done each time
+        for (uint32_t rows = longs; rows != 0u; rows &= rows - 1u) {   // the same for the whole block
+            const int w = __builtin_ctz(rows);
+            const int64_t beg = a.row_ptr[b.p0 + w], end = a.row_ptr[b.p0 + w + 1];
+            bool twice = false;
+            for (uint32_t lo = 0; lo < n; lo += 32u * T) {
+                const uint32_t span = n - lo < 32u * T ? n - lo : 32u * T;
+                for (uint32_t j = threadIdx.x; j < (span + 31u) / 32u; j += 64u * W) tab[j] = 0u;
+                __syncthreads();
+                for (int64_t e = beg + threadIdx.x; e < end; e += 64 * W) {
+                    const uint32_t k = (uint32_t)a.cols[e] - lo, bit = 1u << (k & 31u);
+                    if (k < span && (atomicOr(&tab[k >> 5], bit) & bit)) twice = true;
+                }
+                __syncthreads();
+            }
+            twice = __syncthreads_or(twice);
+            if (wave == w) dup = twice;
+        }
         for (int off = 32; off > 0; off >>= 1) met |= __shfl_xor(met, off, 64);
         if (huge) met = ALL;
         // a conflict is the later row's: lane r tells row r of this one, lane `wave` keeps its own
@@ -549,7 +573,8 @@ __global__ __launch_bounds__(64 * SAP_W_WS, 4) void k_sap_prepare_levels(SapArgs
         __syncthreads();
         if (wave == 0) {
             const uint32_t mine = lane < W ? conf[lane] : 0u;
-            if (lane < W) conf[lane] = 0u;   // (the next batch writes it after its barriers)
+            if (lane < W) conf[lane] = 0u;   // (the next batch writes it and longs after its barriers)
+            if (lane == 0) longs = 0u;
             const uint8_t byte = level_byte<W>(mine, lane);
             if (lane < W && b.p0 + lane < b.s1) a.lev[b.p0 + lane] = byte;
         }
