@@ -336,7 +336,8 @@ pct_status pct_sap_prepare(const pct_csr *A, const pct_sap *p, void *ws_dev, siz
 /* n_iter >= 0 iterations from x_dev (n floats, read and overwritten with the result),
  * after pct_sap_prepare on the same A, parameters and workspace.  Each string is one
  * workgroup, which projects rows that share no column side by side (the result is that of
- * the rows one after another, bit for bit).  Its iterate lives in LDS when n binary32 fit a
+ * the rows one after another, bit for bit where no row repeats a column: the entries of one
+ * that does are added in no fixed order).  Its iterate lives in LDS when n binary32 fit a
  * workgroup's LDS, else in the workspace.  The order is read from order_dev by every call;
  * calls with and without one may follow one another on one workspace.
  * A row's entries are all applied, also where a column repeats in the row; ||a_i|| is

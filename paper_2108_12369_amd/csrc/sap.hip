@@ -20,8 +20,8 @@
 // A string is a chain of row updates, but rows that share no column commute.  A workgroup
 // takes the rows of its string in batches, one row per wave, and projects a batch level by
 // level (k_sap_levels): the same updates of every component of y in the same order, so the
-// result is the one of the rows taken one after another, bit for bit.  Measured per
-// iteration, 100 strings: 640,000 rows of the paper's 200 x 160 system 3.20 -> 0.67 ms
+// result is the one of the rows taken one after another, bit for bit (but for rows that repeat
+// a column, whose entries are added in no fixed order).  Measured per iteration, 100 strings: 640,000 rows of the paper's 200 x 160 system 3.20 -> 0.67 ms
 // (one row at a time before), 368,640 curved rows on 400 x 400 5.85 -> 2.42 ms; with the
 // rows in a random order (nearly every pair shares a column) 2.95 -> 1.54 and 5.93 ->
 // 3.91 ms, since the loads and waits of the other rows leave the chain.
