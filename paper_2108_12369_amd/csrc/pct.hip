@@ -24,6 +24,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <cstdio>
+#include <limits>
 #include <unordered_map>
 #include <vector>
 
@@ -500,6 +501,7 @@ struct RegionDev {
     double c[3], s[3];
     double cr, sr;   // cosine and sine of the region's angle
     double is[3];    // 1 / s
+    double band;     // how near to 1 two ways of computing q may disagree on q <= 1 (region_band)
 };
 struct PhantomArgs {
     int32_t dim, voxelize, n_regions, samples;
@@ -533,11 +535,10 @@ __device__ __forceinline__ double rsp_at(const PhantomArgs &A, const double p[3]
 }
 
 // Whether region g certainly contains (+1) or certainly misses (-1) every point of the
-// box of center m and half-widths e, with a margin of 1e-9 in q (far above the rounding of
-// this bound and of region_q); 0 if the box may meet its boundary.  In the region's frame,
+// box of center m and half-widths e, with the region's band as a margin in q (above the rounding
+// of this bound and of region_q); 0 if the box may meet its boundary.  In the region's frame,
 // scaled by its semi-axes, the box lies within |u_i - um_i| <= ue_i.
 __device__ __forceinline__ int region_box(const RegionDev &g, const double m[3], const double e[3]) {
-    constexpr double EPS = 1e-9;
     double d[3] = {m[0] - g.c[0], m[1] - g.c[1], m[2] - g.c[2]}, w[3] = {e[0], e[1], e[2]};
     if (g.rot) {
         const double d0 = g.cr * d[0] + g.sr * d[1], d1 = g.cr * d[1] - g.sr * d[0];
@@ -557,7 +558,7 @@ __device__ __forceinline__ int region_box(const RegionDev &g, const double m[3],
             qmax = fma(far, far, qmax);
         }
     }
-    return qmax < 1.0 - EPS ? 1 : (qmin > 1.0 + EPS ? -1 : 0);
+    return qmax < 1.0 - g.band ? 1 : (qmin > 1.0 + g.band ? -1 : 0);
 }
 
 // Midpoint ii of S^dim of the voxel idx.
@@ -653,7 +654,7 @@ __global__ void __launch_bounds__(256) k_phantom_area(PhantomArgs A, float *__re
             uint32_t close = 0u;
             for (uint32_t o = open_l; o != 0u; o &= o - 1u) {
                 // scaled coordinates in the region's frame: u_i = b_i + a_i0 tx + a_i1 ty (x, y),
-                // b_2 + a_2 tz (z); within 1e-12 or so of region_q near its boundary
+                // b_2 + a_2 tz (z); within the region's band of region_q near its boundary
                 const RegionDev &g = A.reg[__builtin_ctz(o)];
                 const double d0 = low[0] - g.c[0], d1 = low[1] - g.c[1];
                 const double b0 = fma(g.cr, d0, g.sr * d1) * g.is[0], b1 = fma(g.cr, d1, -(g.sr * d0)) * g.is[1];
@@ -667,7 +668,7 @@ __global__ void __launch_bounds__(256) k_phantom_area(PhantomArgs A, float *__re
                     const double u2 = fma(a2, tz, b2);
                     const double q = fma(u2, u2, fma(u1, u1, u0 * u0));
                     v[u] = q <= 1.0 ? g.rsp : v[u];
-                    close |= !(fabs(q - 1.0) >= 1e-9) ? 1u << u : 0u;   // too close to call (or not a number)
+                    close |= !(fabs(q - 1.0) >= g.band) ? 1u << u : 0u;   // too close to call (or not a number)
                 }
             }
             if (__builtin_amdgcn_ballot_w64(close != 0u) != 0) {   // uniform, rare: tested as it is defined
@@ -1393,6 +1394,21 @@ const char *pct_status_string(pct_status s) {
 
 int32_t pct_version(void) { return 100; }
 
+// RegionDev::band of region g.  A point's coordinates are rounded before the center is taken
+// off, so the scaled ones are off by some roundings of (largest coordinate + |center|) / semi-axis,
+// 32 of them allowing for every way q is computed; with a distance d in u, q near 1 is off by
+// 2 d + d^2.  At least 1e-9, which covers the coordinates and sizes of a phantom in mm; far away or
+// tiny regions have a wider one (infinite at most: every point is tested as it is defined).
+static double region_band(const PhantomArgs &A, const RegionDev &g) {
+    double coord = 0.0, semi = g.s[0];
+    for (int i = 0; i < g.axes; ++i) {
+        coord += fabs(A.o[i]) + (double)A.n[i] * A.h[i] + fabs(g.c[i]);
+        semi = std::min(semi, g.s[i]);
+    }
+    const double d = 32.0 * std::numeric_limits<double>::epsilon() * (coord / semi);
+    return std::max(1e-9, d * (2.0 + d));
+}
+
 pct_status pct_phantom_build(const pct_phantom *ph, float *x_dev, void *stream) {
     pct_status st = check_phantom(ph);
     if (st != PCT_OK) return st;
@@ -1421,6 +1437,7 @@ pct_status pct_phantom_build(const pct_phantom *ph, float *x_dev, void *stream) 
         A.reg[k].cr = A.reg[k].rot ? cos(ang) : 1.0;
         A.reg[k].sr = A.reg[k].rot ? sin(ang) : 0.0;
         for (int i = 0; i < 3; ++i) A.reg[k].is[i] = i < A.reg[k].axes ? 1.0 / r.semi[i] : 0.0;
+        A.reg[k].band = region_band(A, A.reg[k]);
     }
     const int64_t nv = n_voxels(ph);
     const int64_t nL = A.n[A.dim - 1];

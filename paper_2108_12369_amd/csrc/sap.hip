@@ -21,10 +21,11 @@
 // takes the rows of its string in batches, one row per wave, and projects a batch level by
 // level (k_sap_levels): the same updates of every component of y in the same order, so the
 // result is the one of the rows taken one after another, bit for bit (but for rows that repeat
-// a column, whose entries are added in no fixed order).  Measured per iteration, 100 strings: 640,000 rows of the paper's 200 x 160 system 3.20 -> 0.67 ms
-// (one row at a time before), 368,640 curved rows on 400 x 400 5.85 -> 2.42 ms; with the
-// rows in a random order (nearly every pair shares a column) 2.95 -> 1.54 and 5.93 ->
-// 3.91 ms, since the loads and waits of the other rows leave the chain.
+// a column, whose entries are added in no fixed order).  Measured per iteration, 100 strings:
+// 640,000 rows of the paper's 200 x 160 system 3.20 -> 0.67 ms (one row at a time before),
+// 368,640 curved rows on 400 x 400 5.85 -> 2.42 ms; with the rows in a random order (nearly
+// every pair shares a column) 2.95 -> 1.54 and 5.93 -> 3.91 ms, since the loads and waits of the
+// other rows leave the chain.
 //
 // LDS iterate: the metadata of 64 batches lies in the lanes of each wave, and the first 384
 // entries of its next two rows are always in flight.  A row is projected with only as many
