@@ -666,11 +666,13 @@ struct RowOut {
     // stores, so that each kind of access is in flight together.  With packed coordinates
     // (PACK) the column and the brick address are computed from them; an address outside
     // the copy reads element 0.
-    template <bool WB, bool HALF, bool PACK, int G>   // G chunks of 64 entries per group
+    // CST: the constant chord is stored, whatever the lengths are (no arithmetic on them: they
+    // can overflow).  An instance of its own, since a select between the two took 300,001 straight
+    // 3D rows 303 -> 310 us, and a branch around the stores 2.95M curved 2D rows 5.50 -> 5.55 ms.
+    template <bool WB, bool HALF, bool PACK, bool CST, int G>   // G chunks of 64 entries per group
     __device__ __forceinline__ void flush_t(int n, int lane) {
         n = n < STAGE_CAP + 1 ? n : STAGE_CAP + 1;
         const int m = store ? (n < len ? n : len) : 0;   // entries stored
-        const float scale = chord > 0.f ? 0.f : 1.f;
         __builtin_amdgcn_wave_barrier();
         // the wave's output phase runs at a raised issue priority, back to 0 once the row's
         // b is stored (emit_rows_wave): its loads and stores go out while the other waves
@@ -712,7 +714,7 @@ struct RowOut {
                 const int e = g0 + u * WAVE + lane;
                 if (e < m) {
                     // non-temporal: nothing here reads the output again, and x is kept in L2
-                    const float sv = fmaf(__uint_as_float(v[u].y), scale, chord);   // the length, or the chord
+                    const float sv = CST ? chord : __uint_as_float(v[u].y);
                     __builtin_nontemporal_store((int32_t)col[u], &cols[e]);
                     if (HALF) __builtin_nontemporal_store((uint16_t)__half_as_ushort(__float2half_rn(sv)), &vh[e]);
                     else __builtin_nontemporal_store(sv, &vf[e]);
@@ -732,13 +734,18 @@ struct RowOut {
     // coordinates costs some 21 VALU whether it holds entries or not.  (Against groups of 4:
     // 5M curved rows of 307 entries 9.45 -> 9.30 ms, 12 jobs of a batch 7.61 -> 7.49 ms, rows
     // of 164 entries 0.540 -> 0.536, 300,001 of 154 entries 0.323 -> 0.327.  Columns cost 12 a
-    // chunk, where it gained nothing.)
+    // chunk, where it gained nothing.  Constant chords, groups of 4 or 5: 1M curved 3D rows
+    // 1.997 ms with 4 alone, 1.967 so; groups of 3 for them too took 300,001 straight 3D rows
+    // without a chord from 304 to 307 us, for the larger code.)
     template <bool WB, bool HALF, bool PACK>
     __device__ __forceinline__ void flush_g(int n, int lane) {
         const int c = (n + WAVE - 1) / WAVE;
-        if (PACK && (c == 5 || c == 10)) flush_t<WB, HALF, PACK, 5>(n, lane);
-        else if (PACK && (c <= 3 || c == 6 || c == 9)) flush_t<WB, HALF, PACK, 3>(n, lane);
-        else flush_t<WB, HALF, PACK, 4>(n, lane);
+        if (chord > 0.f) {
+            if (PACK && (c == 5 || c == 10)) flush_t<WB, HALF, PACK, true, 5>(n, lane);
+            else flush_t<WB, HALF, PACK, true, 4>(n, lane);
+        } else if (PACK && (c == 5 || c == 10)) flush_t<WB, HALF, PACK, false, 5>(n, lane);
+        else if (PACK && (c <= 3 || c == 6 || c == 9)) flush_t<WB, HALF, PACK, false, 3>(n, lane);
+        else flush_t<WB, HALF, PACK, false, 4>(n, lane);
     }
     template <bool PACK>
     __device__ __forceinline__ void flush_p(int n, int lane) {
