@@ -69,10 +69,11 @@ struct alignas(16) SplP {
 // Stored field by field, with three axes and 368 bytes in 2D too, the count pass of 2,949,120
 // curved 2D rows took 435 us (359 so), the whole call 5.81 ms (5.64); 640,000 straight 2D rows
 // 525 us (517).
+constexpr int FAST_ROW = 1, FAST_WIDE = 2;
 template <typename R, int DIM>
 struct alignas(16) RowV {
     int32_t kind;           // 0: no entry, 1: one ray, 2: ray + spline + ray, 3: per-lane walk
-    int32_t fast;           // every item crosses each axis at most once
+    int32_t fast;           // 0, or every item crosses each axis at most once: FAST_ROW, or FAST_WIDE
     double bfac;            // WEPL noise factor 1 + r z
     int32_t M[4];           // items of ray[0] and ray[1] (0 when it misses the box), of the spline
     RayP<R, DIM> ray[2];    // ray[0]: the straight path, or the ray into the entry point
@@ -791,13 +792,14 @@ struct FastWalk {
 // lane stores on every item without a branch.
 // The emit of curved rows is bound by the issue of these instructions, so they are counted:
 // slots kept as byte offsets (one and-or per store; `in`: the slice's offset mask, in a
-// register, `base`: the slice's address, a multiple of its size), the column steps as 24-bit products (a 32-bit one takes four issue
-// slots; setup_row lets no grid with a stride of 2^23 or more in here) and the number of
-// crossings as a sum of squares.  This and
+// register, `base`: the slice's address, a multiple of its size), the column steps as 24-bit
+// products (a 32-bit one takes four issue slots; WIDE: a grid with a column stride of 2^23 or
+// more, which needs those: 200,000 rows on planes of 3072 x 3072 voxels 0.64 ms, 0.73 through the
+// general item) and the number of crossings as a sum of squares.  This and
 // the item ends of wave_row took an item from 77 to 70 (2D) and from 120 to 108 VALU (3D):
 // 100,003 curved 3D rows without A 266 -> 257 us, 1M on 200 x 200 x 160 2.19 -> 2.14 ms,
 // 2.95M on 400 x 400 6.15 -> 6.03 ms (the waves wait longer on memory instead).
-template <typename R, int DIM>
+template <typename R, int DIM, bool WIDE>
 __device__ __forceinline__ void item_fast(const float hf[3], const int32_t stride[3], const int Ip[3], const R Fp[3],
                                           const int Ie[3], const R Fe[3], FastWalk &wk, uint32_t in, uint32_t base) {
     float lam[3] = {2.f, 2.f, 2.f}, dn2 = 0.f;
@@ -816,7 +818,7 @@ __device__ __forceinline__ void item_fast(const float hf[3], const int32_t strid
         // in [0, 1] (a NaN from a vanishing displacement becomes 1: the item's end)
         const float l = fminf(fabsf(dist) * __builtin_amdgcn_rcpf(fabsf(dff)), 1.f);
         lam[d] = di != 0 ? l : 2.f;
-        dc[d] = d == 0 ? di : __mul24(di, stride[d]);
+        dc[d] = d == 0 ? di : WIDE ? di * stride[d] : __mul24(di, stride[d]);
         tot += (uint32_t)__mul24(di, di);
     }
     const float len = __builtin_amdgcn_sqrtf(dn2);
@@ -974,10 +976,10 @@ __device__ __forceinline__ void stage_strides(const JobDev &J, int32_t stride[3]
 }
 
 // Walk one row with the whole wave; n_entries = entries produced.
-// FAST: every item crosses each axis at most once (the row's `fast` flag).
+// FAST: every item crosses each axis at most once (the row's `fast` flag); WIDE: FAST_WIDE.
 // RAY: a straight row (kind 1) with FAST: every lane takes the one ray, whose constants
 // are the same in all lanes.
-template <typename R, int DIM, typename TW, bool FAST, bool RAY = false>
+template <typename R, int DIM, typename TW, bool FAST, bool RAY = false, bool WIDE = false>
 __device__ __forceinline__ void wave_row(const JobDev &J, LdsRow wl, int kind, RowOut<TW> &out,
                                          int lane, int64_t &n_entries) {
     // item counts as the count pass writes them; the bounds only matter for a
@@ -1134,7 +1136,7 @@ __device__ __forceinline__ void wave_row(const JobDev &J, LdsRow wl, int kind, R
             } else {
                 piece_at<R, DIM>(P, t, Fe);
                 piece_voxel<R, DIM>(P, Fe, Ie, fre);
-                if (FAST) item_fast<R, DIM>(hf, stride, Ip, Fp, Ie, Fe, fw, slice, sbase);
+                if (FAST) item_fast<R, DIM, WIDE>(hf, stride, Ip, Fp, Ie, Fe, fw, slice, sbase);
                 else item_general<R, DIM>(hf, stride, Ip, Fp, frp, Ie, Fe, wk, close);
             }
 #pragma unroll
@@ -1322,8 +1324,8 @@ __device__ __forceinline__ RowSetup setup_row(const JobDev &J, int64_t g, RowRef
     if (J.path == 1) make_path<R, DIM, true>(J, g, p, noise, &zn);
     else make_path<R, DIM, false>(J, g, p, noise, &zn);
     const R ninf = -r_inf<R>(), pinf = r_inf<R>();
-    // fast: every item crosses each axis at most once (and item_fast's column steps hold)
-    int kind = 0, fast = (DIM == 3 ? (int64_t)J.n[0] * J.n[1] : (int64_t)J.n[0]) < (1 << 23) ? 1 : 0;
+    // fast: every item crosses each axis at most once
+    int kind = 0, fast = (DIM == 3 ? (int64_t)J.n[0] * J.n[1] : (int64_t)J.n[0]) < (1 << 23) ? FAST_ROW : FAST_WIDE;
     int64_t cross = 0;        // face crossings of the pieces
     bool any = false;         // a piece with items
     int32_t M0 = 0, M1 = 0, Ns = 0;
@@ -1508,12 +1510,14 @@ __device__ __forceinline__ void emit_rows_wave(const JobDev &J, char *rowbuf, in
         if (mine && kind != 0) {
             if constexpr (std::is_same<R, double>::value) {
                 if (kind == 1) wave_ray_row<DIM, TW>(J, row_ref<R, DIM>(rowbuf, J, r), wl, out, lane, ne);
-                else if (fast) wave_row<R, DIM, TW, true>(J, wl, kind, out, lane, ne);
+                else if (fast == FAST_ROW) wave_row<R, DIM, TW, true>(J, wl, kind, out, lane, ne);
+                else if (fast) wave_row<R, DIM, TW, true, false, true>(J, wl, kind, out, lane, ne);
                 else wave_row<R, DIM, TW, false>(J, wl, kind, out, lane, ne);
             } else {
                 if (fast) {
                     if (kind == 1) wave_row<R, DIM, TW, true, true>(J, wl, kind, out, lane, ne);
-                    else wave_row<R, DIM, TW, true>(J, wl, kind, out, lane, ne);
+                    else if (fast == FAST_ROW) wave_row<R, DIM, TW, true>(J, wl, kind, out, lane, ne);
+                    else wave_row<R, DIM, TW, true, false, true>(J, wl, kind, out, lane, ne);
                 } else {
                     wave_row<R, DIM, TW, false>(J, wl, kind, out, lane, ne);
                 }
