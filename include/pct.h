@@ -246,7 +246,8 @@ pct_status pct_set_launch_config(const pct_launch_config *cfg);
 pct_status pct_get_launch_config(pct_launch_config *cfg);
 
 /* Autotuner: runs pct_count_rows once and then pct_emit_csr with every candidate
- * configuration (rows_per_wave 16/32/64 x both orders x blocks_per_cu 0/4), timing each
+ * configuration (rows_per_wave 16/32/64 x both orders x blocks_per_cu 0/4; of rows_per_wave
+ * values that a small batch runs alike, the largest), timing each
  * emit with HIP events on `stream` (this call synchronises it), keeps the fastest as the
  * process-wide configuration and returns it in *best.  The jobs must be ready for
  * pct_emit_csr (outputs sized from an earlier count); their outputs hold a complete,

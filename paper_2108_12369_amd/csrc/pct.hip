@@ -1675,7 +1675,11 @@ pct_status pct_autotune(int32_t n_jobs, const pct_job *jobs, void *ws, size_t ws
         (void)hipEventDestroy(e0);
         return PCT_EHIP;
     }
-    const int rpws[3] = {16, 32, 64};
+    // a batch too small for some of the settings runs them alike (rows_per_wave): only the
+    // largest of those is timed, or the luckiest of equals would be kept and cached
+    const int rpws[3] = {64, 32, 16};
+    int64_t total_rows = 0;
+    for (int32_t j = 0; j < n_jobs; ++j) total_rows += jobs[j].beam->row_count;
     const int orders[2] = {PCT_ORDER_GIVEN, PCT_ORDER_LPT};
     const int bpcs[2] = {0, 4};
     float best_ms = -1.f;
@@ -1683,6 +1687,7 @@ pct_status pct_autotune(int32_t n_jobs, const pct_job *jobs, void *ws, size_t ws
     for (int q = 0; q < 2 && st == PCT_OK; ++q) {
         for (int o = 0; o < 2 && st == PCT_OK; ++o) {
             for (int r = 0; r < 3 && st == PCT_OK; ++r) {
+                if (r > 0 && rows_per_wave(rpws[r], total_rows) == rows_per_wave(rpws[r - 1], total_rows)) continue;
                 g_cfg = pct_launch_config{rpws[r], orders[o], bpcs[q]};
                 float ms = 0.f;
                 for (int rep = 0; rep < 2 && st == PCT_OK; ++rep) {
