@@ -731,8 +731,9 @@ struct RowOut {
         }
         __builtin_amdgcn_wave_barrier();
     }
-    // Groups of 3, 4 or 5 chunks, whichever leaves the fewest past the row: a chunk of packed
-    // coordinates costs some 21 VALU whether it holds entries or not.  (Against groups of 4:
+    // Groups of 3, 4 or 5 chunks, whichever leaves the fewest past a row of up to 12 chunks (longer
+    // rows take groups of 4): a chunk of packed coordinates costs some 21 VALU whether it holds
+    // entries or not.  (Against groups of 4:
     // 5M curved rows of 307 entries 9.45 -> 9.30 ms, 12 jobs of a batch 7.61 -> 7.49 ms, rows
     // of 164 entries 0.540 -> 0.536, 300,001 of 154 entries 0.323 -> 0.327.  Columns cost 12 a
     // chunk, where it gained nothing.  Constant chords, groups of 4 or 5: 1M curved 3D rows

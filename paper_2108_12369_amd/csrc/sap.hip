@@ -423,31 +423,35 @@ __global__ __launch_bounds__(64 * W) void k_sap_levels(SapArgs a, uint32_t span)
 // k_sap_prepare and k_sap_levels in one pass over A, for the natural order (whose batches hold
 // every row once).  One block per batch, a wave per row.  The rows meet in an LDS table of T
 // words: every entry writes its name (its column's high bits, its row, its place in the row) to
-// its column's word, then reads the word back.  An entry that finds its own
-// name is done; one that finds another of the same column has met that row, or its own: the row
-// repeats a column, and the entry is done too, since that one stands for both.  Those that lost
-// write again, and so on until all are done: of any two entries of one column in two rows, the
-// later to be done met the other.  Nothing is cleared, since a word is only read by those that
-// wrote it, and no column is out of the table's range.  The word is the column modulo T, moved
-// on by 35 at each turn: in effect modulo T - 35, a prime, while it and the high bits still give
-// the column.  Modulo T a steep path on a grid of 512 voxels per row meets 32 words only, and
-// each round finishes one entry of a word: 50,000 steep rows on 512 x 320 (where column
-// bitmaps had taken 0.150 ms) 0.209 -> 0.143 ms, on 1024 x 1024 0.98 -> 0.40, on 2048 x 2048 4.9
-// -> 1.01; 100,000 curved rows on 400 x 400 0.288 and 0.290.  The columns and values of the block's
-// next batch are loaded meanwhile, those of its next but one are located.
+// its column's word, then reads the word back.  An entry that finds its own name is done; one
+// that finds another of the same column has met that row, or its own: the row repeats a column,
+// and the entry is done too, since that one stands for both.  Those that lost write again, and
+// so on until all are done: of any two entries of one column in two rows, the later to be done
+// met the other.  Nothing is cleared, since a word is only read by those that wrote it, and no
+// column is out of the table's range.  The columns and values of the block's next batch are
+// loaded meanwhile, those of its next but one are located.
+//
+// The word is the column modulo T, moved on by 35 at each turn of T columns, which is nearly the
+// column modulo T - 35, a prime; it and the high bits give the column.  Modulo T a steep path on
+// a grid of 512 voxels per row meets 32 words only, and each round finishes one entry of a word:
+// 50,000 steep rows on 512 x 320 (where column bitmaps had taken 0.150 ms) 0.209 -> 0.143 ms,
+// on 1024 x 1024 0.98 -> 0.40, on 2048 x 2048 4.9 -> 1.01; 100,000 curved rows on 400 x 400 0.288
+// and 0.290.
 //
 // Bound by the barriers of a batch (three and two per further round; two blocks per CU).  100
-// strings of 176M entries in 160,000 columns: k_sap_prepare, whose hash table takes an LDS
-// atomic per entry, 1.53 ms, then k_sap_levels, whose masks go twice over the columns, 0.72;
-// this 0.93.  With masks set and read here instead 1.20.  With 16 rows per batch (y in LDS) it
-// is no faster than the two: 104M entries in 32,000 columns 0.97 and 0.96 ms.
-// The hash table's limit of 1,024 columns per row is not one here: 20,000 rows of 1,283 entries
-// 28.9 -> 0.31 ms (the longer rows had counted as repeating a column).
+// strings of 176M entries in 160,000 columns: k_sap_prepare, whose column bitmaps take an LDS
+// atomic per entry, 1.53 ms, then k_sap_levels, which reads the columns again and sets, reads and
+// clears its masks, 0.72; this 0.93.  With masks set and read here instead 1.20.  With 16 rows
+// per batch (y in LDS) it is no faster than the two: 104M entries in 32,000 columns 0.97 and
+// 0.96 ms.  Where the bitmaps do not fit LDS (above 163,840 columns) k_sap_prepare has a hash
+// table, whose limit of 1,024 columns per row is not one here: 20,000 rows of 1,283 entries 28.9
+// -> 0.31 ms (the longer rows had counted as repeating a column).
+//
 // A row of more than MAX_LEN entries is taken to meet every other row of its batch (each of its
 // entries would have to be named), but whether it repeats a column is found: the block sets its
-// columns in the table as a bitmap, 2^19 columns at a time.  Taken as repeating one, it
-// would be projected with atomic adds, and its norm found by store_coef in quadratic time: 2,000
-// rows of 5,000 entries in 100,000 columns 53.7 ms, 0.105 so.
+// columns in the table as a bitmap, 2^19 columns at a time.  Taken as repeating one, it would
+// be projected with atomic adds, and its norm found by store_coef in quadratic time: 2,000 rows
+// of 5,000 entries in 100,000 columns 53.7 ms, 0.105 so.
 template <typename VT>
 __global__ __launch_bounds__(64 * SAP_W_WS, 4) void k_sap_prepare_levels(SapArgs a, float relax) {
     constexpr int W = SAP_W_WS, U = 8;         // U: chunks of 64 entries of the row kept in registers
